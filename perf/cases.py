@@ -1,0 +1,235 @@
+"""Decode steps as a serving process issues them: the workloads this library is timed on.
+
+A case is one shard (its widths, storage formats and layouts), a batch, a context and an execution mode.  `prepare` does
+what a server does once -- allocate and fill weights and cache, create the library context, hand over the pointers, set the
+policy -- and `run` is one decode step through the C ABI.  A step is idempotent (it writes the slot of the current token
+and never advances the lengths), so it can be repeated on the same state.
+"""
+import random
+
+import torch
+
+from paper_2501_08192_amd import binding as psv
+from paper_2501_08192_amd import synth
+from paper_2501_08192_amd.harness import default_policy
+
+# Shards of the benchmark workloads and of the batch x context map: hidden, local q heads, local kv heads, local FFN width.
+SHARDS = {
+    "small": (1024, 8, 8, 2816),     # the small multi-head decoder
+    "8b-tp8": (4096, 4, 1, 1792),    # 8B-shaped model on 8 devices
+    "8b-tp4": (4096, 8, 2, 3584),    # ... on 4 devices
+    "70b-tp8": (8192, 8, 1, 3584),   # 70B-shaped model on 8 devices
+    "70b-tp4": (8192, 16, 2, 7168),  # ... on 4 devices: 2 local kv heads
+}
+
+# How a step runs (a case's mode).  "on": communication windows with the benchmark's default policy (first consumer launched
+# into its window, the rest prefetched into the cache); "cache": the published scheme, every planned byte goes to the cache;
+# "plain": no windows, no prefetch (a model on one device, or a caller that runs its collectives itself); "static": the same
+# through the entry point that needs no context.
+
+
+def _case(shard, layers, batch, context, mode, window=0.0, ragged=False, paged=False, weights="bf16", kv="bf16",
+          kv_layout="head", weight_layout="row", **name):
+    return dict(shard=shard, layers=layers, batch=batch, context=context, mode=mode, window=window, ragged=ragged, paged=paged,
+                weights=weights, kv=kv, kv_layout=kv_layout, weight_layout=weight_layout, **name)
+
+
+def listed():
+    return [
+        # one user of a small model, short chat: launches and latency
+        _case("small", 2, 1, 256, "on", 10.0, name="small_b1_t256"),
+        # one user of an 8B-shaped model on 8 devices, all layers: the configuration the headline number is quoted on
+        _case("8b-tp8", 32, 1, 2048, "on", 15.0, name="8b_tp8_b1_t2048"),
+        # two users through the context-free entry point of callers that may not allocate; an odd context
+        _case("8b-tp4", 8, 2, 777, "static", name="8b_tp4_b2_t777_static"),
+        # one user of a 70B-shaped model with a long document
+        _case("70b-tp8", 8, 1, 16384, "on", 20.0, name="70b_tp8_b1_t16384"),
+        # a few users whose sequences differ in length, paged cache, row-major weights as loaded, published prefetch scheme
+        _case("8b-tp8", 8, 5, 3001, "cache", 15.0, ragged=True, paged=True, name="8b_tp8_b5_ragged_cache"),
+        # a small batch on a 70B-shaped shard
+        _case("70b-tp8", 8, 8, 4096, "on", 20.0, weight_layout="tiled", name="70b_tp8_b8_t4096"),
+        # the same in int8, weights and cache
+        _case("70b-tp8", 8, 8, 4096, "on", 20.0, weights="int8", kv="int8", weight_layout="tiled", name="70b_tp8_b8_t4096_int8"),
+        # two local kv heads, token-major cache of mixed lengths, no windows
+        _case("70b-tp4", 4, 16, 2500, "plain", ragged=True, kv_layout="token", name="70b_tp4_b16_ragged_plain"),
+        # many users with short contexts: the projections decide
+        _case("70b-tp4", 4, 64, 1024, "on", 20.0, weight_layout="tiled", name="70b_tp4_b64_t1024"),
+        # many users, paged: the cache decides
+        _case("8b-tp8", 4, 64, 8192, "on", 25.0, paged=True, weight_layout="tiled", name="8b_tp8_b64_t8192_paged"),
+        # an odd batch of mixed lengths in int8, paged, no windows
+        _case("8b-tp4", 8, 39, 6000, "plain", ragged=True, paged=True, weights="int8", kv="int8", weight_layout="tiled",
+              name="8b_tp4_b39_ragged_int8_plain"),
+        # the largest: a 70B-shaped shard, long contexts, more per layer than the on-chip cache holds
+        _case("70b-tp8", 4, 32, 32768, "on", 20.0, paged=True, weight_layout="tiled", name="70b_tp8_b32_t32768_paged"),
+    ]
+
+
+MAX_BYTES = 2.9e9      # of a drawn case: just under the largest listed one
+
+
+def draw(rng):
+    """Shards, batches 1-64, contexts 1-32768 (16 and more for an int8 cache), every mode, format and layout."""
+    while True:
+        shard = rng.choice(sorted(SHARDS))
+        batch = min(64, int(2.0 ** rng.uniform(0.0, 6.05)))
+        kv = "int8" if rng.random() < 0.3 else "bf16"
+        low = 4.0 if kv == "int8" else 0.0
+        context = min(32768, int(2.0 ** rng.uniform(low, 15.0)) + rng.choice([0, 0, 1, 5]))
+        mode = rng.choice(["on", "on", "on", "cache", "plain", "plain", "static"])
+        case = _case(shard, rng.randint(2, 12), batch, context, mode,
+                     window=rng.choice([10.0, 15.0, 20.0, 25.0]) if mode in ("on", "cache") else 0.0,
+                     ragged=batch > 1 and rng.random() < 0.5, paged=rng.random() < 0.5,
+                     weights="int8" if rng.random() < 0.3 else "bf16", kv=kv,
+                     kv_layout="token" if kv == "bf16" and rng.random() < 0.2 else "head",
+                     weight_layout="tiled" if batch >= 3 and rng.random() < 0.6 else "row")
+        w = _workload(case)
+        # the shard of a case is whole; the cache is allocated for `context` tokens of every sequence
+        if case["layers"] * w.layer_bytes > MAX_BYTES:
+            continue
+        if mode == "static" and psv.psv_workspace_bytes(_desc(case)) > psv.PSV_STATIC_SCRATCH_BYTES:
+            continue
+        return case
+
+
+def _workload(case):
+    hidden, nq, nkv, ffn = SHARDS[case["shard"]]
+    return synth.Workload("case", case["layers"], hidden, nq, nkv, 128, ffn, case["batch"], case["context"], case["paged"],
+                          (case["window"], case["window"]), weight_format=case["weights"], kv_format=case["kv"],
+                          kv_layout=case["kv_layout"], weight_layout=case["weight_layout"])
+
+
+def _desc(case):
+    w = _workload(case)
+    return psv.model_desc(w.n_layers, w.hidden, w.n_q_heads, w.n_kv_heads, w.ffn, w.batch, (w.context + 15) // 16 * 16,
+                          rms_eps=w.rms_eps, rope_theta=w.rope_theta, weight_format=w.weight_format, kv_format=w.kv_format,
+                          kv_layout=w.kv_layout, weight_layout=w.weight_layout)
+
+
+def _lens(case):
+    """Attention spans: all equal to the context (static batching), or spread over it evenly on a logarithmic scale."""
+    b, t = case["batch"], case["context"]
+    if not case["ragged"]:
+        return [t] * b
+    rng = random.Random(b * 65537 + t)
+    lens = [max(1, min(t, int(round(t * 2.0 ** rng.uniform(-4.0, 0.0))))) for _ in range(b)]
+    lens[rng.randrange(b)] = t
+    return lens
+
+
+_PAIR = []      # the process's two streams: one server runs its steps one after the other, whatever context they belong to
+
+
+def _streams(desc):
+    """Two streams that run side by side (HIP multiplexes streams onto a few hardware queues, and not every pair does)."""
+    if not _PAIR:
+        spare, main = [], torch.cuda.Stream()
+        for _ in range(8):
+            side = torch.cuda.Stream()
+            spare.append(side)
+            ctx = psv.psv_create(desc, main, side)
+            good = psv.psv_check_overlap(ctx)
+            psv.psv_destroy(ctx)
+            if good:
+                break
+        _PAIR.extend([main, side, spare])
+    return _PAIR[0], _PAIR[1]
+
+
+class State:
+    """One shard resident on the GPU and the library context on it."""
+
+    def __init__(self, case, seed):
+        self.case = case
+        w = self.w = _workload(case)
+        dev = "cuda"
+        desc = self.desc = _desc(case)
+        self.main, side = _streams(desc)
+        self.ctx = None
+        if case["mode"] != "static":
+            self.ctx = psv.psv_create(desc, self.main, side)
+            if case["mode"] == "on":
+                for _ in range(3):
+                    if psv.psv_check_overlap(self.ctx):
+                        break
+        self.weights, pools = [], []
+        current = torch.cuda.current_stream()
+        for l in range(w.n_layers):
+            lw = synth.layer_weights(w, l, seed, dev)
+            if w.weight_layout == "tiled":
+                for n in ("w_qkv", "w_o", "w_gate", "w_up", "w_down"):
+                    src, dst = lw[n], torch.empty_like(lw[n])
+                    psv.psv_tile_weights(dst, src, src.shape[0], src.shape[1], w.weight_format, current)
+                    lw[n] = dst
+            self.weights.append(lw)
+            k, v = synth.kv_pools(w, l, seed, dev)
+            if not pools:      # one allocation for the pools of all layers
+                pools = [torch.empty((w.n_layers,) + t.shape, dtype=t.dtype, device=dev) for t in (k, v)]
+            pools[0][l].copy_(k)
+            pools[1][l].copy_(v)
+        self.k, self.v = pools
+        self.page_table = synth.page_table(w, seed).to(dev) if w.paged else None
+        lens = _lens(case)
+        self.seq_lens = torch.tensor(lens, dtype=torch.int32, device=dev)
+        self.x_in = synth.x_in(w, seed, dev)
+        self.x_out = torch.empty_like(self.x_in)
+        self.k_list, self.v_list = list(self.k), list(self.v)
+        if self.ctx is not None:
+            for l, lw in enumerate(self.weights):
+                psv.psv_set_layer_weights(self.ctx, l, lw)
+            psv.psv_set_kv(self.ctx, self.k_list, self.v_list, self.page_table, w.blocks_per_seq, w.pool_blocks, self.seq_lens)
+            psv.psv_set_comm_windows(self.ctx, case["window"], case["window"])
+            policy = (psv.prefetch_policy(mode=0) if case["mode"] == "plain"
+                      else default_policy(w, prelaunch=1 if case["mode"] == "on" else 0))
+            psv.psv_set_policy(self.ctx, policy, w.batch, max(lens))
+        torch.cuda.synchronize()
+
+    def __del__(self):
+        if getattr(self, "ctx", None) is not None:
+            try:
+                psv.psv_sync(self.ctx)
+            finally:
+                psv.psv_destroy(self.ctx)
+                self.ctx = None
+
+
+def prepare(case, seed):
+    return State(case, seed)
+
+
+def run(state):
+    w = state.w
+    if state.ctx is not None:
+        psv.psv_decode_step(state.ctx, state.x_in, state.x_out, w.batch, 0, w.n_layers)
+    else:
+        psv.psv_decode_step_static(state.desc, state.weights, state.k_list, state.v_list, state.page_table, w.blocks_per_seq,
+                                   w.pool_blocks, state.seq_lens, state.x_in, state.x_out, w.batch, 0, w.n_layers, state.main)
+    return {"x": state.x_out, "k": state.k, "v": state.v}      # the residual stream and the cache with the new rows in it
+
+
+def work(case):
+    """Every weight once, K and V of the attended spans once, the residual stream in and out; multiply-adds of the projections
+    and of attention.  The communication windows move nothing and are not counted."""
+    w = _workload(case)
+    hidden, nq, nkv, ffn = SHARDS[case["shard"]]
+    tokens = sum(_lens(case))
+    kv_per_token = nkv * (2 * (128 + 4) if case["kv"] == "int8" else 2 * 2 * 128)
+    per_layer = w.weight_bytes_per_layer + 2 * 2 * hidden + kv_per_token * (tokens + case["batch"])      # gains; new rows
+    if case["weights"] == "int8":
+        per_layer += 4 * (w.qkv_rows + 2 * hidden + 2 * ffn)
+    elements = w.qkv_rows * hidden + hidden * nq * 128 + 3 * ffn * hidden
+    flops = w.n_layers * (2.0 * case["batch"] * elements + 4.0 * nq * 128 * tokens)
+    return {"bytes": float(w.n_layers * per_layer + 2 * 4 * case["batch"] * hidden), "flops": flops}
+
+
+def tolerance(case):
+    """Sums are fp32.  What moves a result more than their order is rounding of stored rows: a new key or value lands on
+    either side of a bf16 boundary (one place in the last is up to 2^-7 of the value) or of an int8 code, and a sequence of
+    few tokens passes that on undiluted; int8 weights take their activations as two int8 digits (15 bits of a block's largest
+    element).  About four times the distance of the present path from the same steps in 64 bits: 1e-5 for bf16 storage and
+    spans of hundreds of tokens, 4e-4 for spans of a few; 4e-4 and 9e-4 with int8."""
+    q8 = case["weights"] == "int8" or case["kv"] == "int8"
+    short = min(_lens(case)) < 128
+    t = {"rel": (4e-3 if short else 2e-3) if q8 else (1.6e-3 if short else 1e-4), "max": 0.03 if short or q8 else 0.016}
+    if case["kv"] == "int8":
+        t["differ"] = 5e-3
+    return t
