@@ -2,8 +2,8 @@
 
 A case is one shard (its widths, storage formats and layouts), a batch, a context and an execution mode.  `prepare` does
 what a server does once -- allocate and fill weights and cache, create the library context, hand over the pointers, set the
-policy -- and `run` is one decode step through the C ABI.  A step is idempotent (it writes the slot of the current token
-and never advances the lengths), so it can be repeated on the same state.
+policy -- and `run` is one decode step through the C ABI, `exact` the same step in 64 bits.  A step is idempotent (it
+writes the slot of the current token and never advances the lengths), so it can be repeated on the same state.
 """
 import random
 
@@ -233,3 +233,88 @@ def tolerance(case):
     if case["kv"] == "int8":
         t["differ"] = 5e-3
     return t
+
+
+def _rotate(t, angle):
+    """Rotary embedding of [..., 128] rows: channel f pairs with f + 64."""
+    lo, hi = t[..., :64], t[..., 64:]
+    c, s = torch.cos(angle), torch.sin(angle)
+    return torch.cat([lo * c - hi * s, hi * c + lo * s], dim=-1)
+
+
+def _quantised(row):
+    """An int8 cache's row as it is stored, symmetric codes with one scale: (codes, scale)."""
+    scale = (row.abs().amax() / 127.0).float()
+    scale = torch.where(scale > 0, scale, torch.ones_like(scale))
+    return torch.round(row.float() / scale).clamp(-127, 127), scale
+
+
+def exact(case, seed):
+    """The step in 64 bits from the same inputs.  The new key and value rows pass into attention as the cache stores them;
+    they come back unrounded, and not at all where they are bytes."""
+    w, dev, lens = _workload(case), "cuda", _lens(case)
+    hidden, nq, nkv, ffn = SHARDS[case["shard"]]
+    q8, token = case["kv"] == "int8", case["kv_layout"] == "token"
+    x = synth.x_in(w, seed, dev).double()
+    last = torch.tensor(lens, dtype=torch.float64, device=dev) - 1
+    freq = w.rope_theta ** (-torch.arange(64, dtype=torch.float64, device=dev) / 64)
+    angle = (last[:, None] * freq)[:, None, :]
+    table = (synth.page_table(w, seed) if w.paged else torch.arange(w.pool_blocks).reshape(w.batch, -1)).to(dev).long()
+    ks, vs = [], []
+
+    def norm(t, gain):
+        return t / torch.sqrt((t * t).mean(dim=-1, keepdim=True) + w.rms_eps) * gain.double()
+
+    def heads(pool, blocks, t, channel_major):
+        """Rows [nkv, t, 128] of one sequence."""
+        if q8:
+            p = pool[blocks]
+            scale = p[:, :, 2048:].contiguous().view(torch.float32).double()
+            codes = p[:, :, :2048].contiguous().view(torch.int8).double()
+            p = codes.view(-1, nkv, 128, 16).transpose(2, 3) if channel_major else codes.view(-1, nkv, 16, 128)
+            p = p * scale[..., None]
+        else:
+            p = pool[blocks].double()
+            p = p.transpose(1, 2) if token else p.transpose(2, 3) if channel_major else p
+        return p.transpose(0, 1).reshape(nkv, -1, 128)[:, :t].clone()
+
+    for l in range(w.n_layers):
+        lw = synth.layer_weights(w, l, seed, dev)
+
+        def project(t, name):
+            m = lw[name].double()
+            if case["weights"] == "int8":
+                m = m * lw["s_" + name[2:]].double()[:, None]
+            return t @ m.T
+
+        k_pool, v_pool = synth.kv_pools(w, l, seed, dev)
+        qkv = project(norm(x, lw["g_attn"]), "w_qkv").view(w.batch, nq + 2 * nkv, 128)
+        q, k, v = _rotate(qkv[:, :nq], angle), _rotate(qkv[:, nq:nq + nkv], angle), qkv[:, nq + nkv:]
+        out = torch.empty_like(q)
+        for b, t in enumerate(lens):
+            blocks = table[b, :(t + 15) // 16]
+            kr, vr = heads(k_pool, blocks, t, False), heads(v_pool, blocks, t, True)
+            for h in range(nkv):
+                for rows, new in ((kr, k), (vr, v)):
+                    if q8:
+                        code, scale = _quantised(new[b, h])
+                        rows[h, t - 1] = code.double() * scale.double()
+                    else:
+                        rows[h, t - 1] = new[b, h].float().bfloat16().double()
+            p = torch.softmax(q[b].view(nkv, nq // nkv, 128) @ kr.transpose(1, 2).contiguous() / 128 ** 0.5, dim=-1)
+            out[b] = (p @ vr).reshape(nq, 128)
+        if not q8:
+            kd, vd = k_pool.double(), v_pool.double()
+            for b, t in enumerate(lens):
+                blk, r = table[b, (t - 1) // 16], (t - 1) % 16
+                if token:
+                    kd[blk, r], vd[blk, r] = k[b], v[b]
+                else:
+                    kd[blk, :, r], vd[blk, :, :, r] = k[b], v[b]
+            ks.append(kd)
+            vs.append(vd)
+        y = x + project(out.reshape(w.batch, -1), "w_o")
+        h = norm(y, lw["g_mlp"])
+        gate = project(h, "w_gate")
+        x = y + project(gate * torch.sigmoid(gate) * project(h, "w_up"), "w_down")
+    return {"x": x, "k": None if q8 else torch.stack(ks), "v": None if q8 else torch.stack(vs)}
