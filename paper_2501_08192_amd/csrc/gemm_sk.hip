@@ -206,8 +206,8 @@ __device__ __forceinline__ void sk_read_sums(const SkWaitArgs &wt, int n_ent, in
 // 64-element K slabs.  Per slab the activations of all batch entries (hi and lo bf16 planes) are brought
 // into LDS once, in MFMA fragment order, and every wave reads its B-fragments from there, so the 16-byte
 // global loads of a wave are spent on weights only: 32 contiguous bytes per lane per row tile, i.e. whole
-// 128-byte lines of 16 rows.  Weight fragments are prefetched PF slabs ahead through a register ring and
-// the activation slab two slabs ahead, which keeps 16 KiB per wave in flight even when only a few
+// 128-byte lines of 16 rows.  Weight fragments and activation slabs are prefetched PF slabs ahead through
+// register rings, which keeps 16 KiB of weights per wave in flight even when only a few
 // workgroups exist (small matrices at batch 64 cannot use many: every extra K split costs a partial
 // result of batch x rows floats).  Splits are summed later in split order by the consumer (k_sk_reduce or
 // k_resid_sum): deterministic, no atomics.
@@ -240,7 +240,7 @@ struct GemmSkArgs {
 __device__ __forceinline__ uint32_t xor4(uint4 v) { return v.x ^ v.y ^ v.z ^ v.w; }
 
 template <int NB, int HOLD>
-__global__ __launch_bounds__(256) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj)
+__global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj)
 {
     constexpr bool WAIT = HOLD > 0;
     static_assert(!WAIT || NB <= 2, "the waiting variant is built for one or two batch tiles");
@@ -288,13 +288,13 @@ __global__ __launch_bounds__(256) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj)
             f.a1[mt] = ld16(wp[mt] + (size_t)s * wstep + whalf);
         }
     };
-    // activation slab: NB*256 16-byte units, unit u = ((tile*2 + plane)*16 + row)*8 + segment
+    // activation slab: NB*256 16-byte units, unit u = ((tile*2 + plane)*16 + row)*8 + segment.  A thread has the same plane, row
+    // and segment of every tile: one 32-bit offset from uniform bases serves all its loads (both planes are far below 4 GiB).
+    const uint32_t x_off = (uint32_t)(((size_t)(tid >> 7) * a.x_plane + (size_t)((tid >> 3) & 15) * K + (tid & 7) * 8) * 2);
     auto load_slab = [&](int s, uint4 (&r)[NB]) {
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const int u = tid + j * 256, n = u >> 8, p = (u >> 7) & 1, row = (u >> 3) & 15, seg = u & 7;
-            r[j] = ld16(a.xb + (size_t)p * a.x_plane + (size_t)(n * 16 + row) * K + (size_t)s * 64 + seg * 8);
-        }
+        for (int j = 0; j < NB; ++j)
+            r[j] = ld16(reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(a.xb + ((size_t)j * 16 * K + (size_t)s * 64)) + x_off));
     };
     auto store_slab = [&](int buf, const uint4 (&r)[NB]) {
 #pragma unroll
@@ -360,28 +360,35 @@ __global__ __launch_bounds__(256) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj)
     }
     WFrag wq[PF];
 #pragma unroll
-    for (int q = 0; q < PF; ++q)
-        if (s0 + q < s1) load_w(s0 + q, wq[q]);
+    for (int q = 0; q < PF; ++q) {
+        if (!WAIT) load_w_all(min(s0 + q, s1 - 1), wq[q]);
+        else if (s0 + q < s1) load_w(s0 + q, wq[q]);
+    }
     __shared__ float ssq_s[WAIT ? kSkWaitEntries : 1];
     if (WAIT) {     // the weights above travel, then sit on chip, while the window runs
         if (w == 0) sk_wait_for_operand(a.wt, a.batch, K, s0, s1, lane);     // one wave polls
         __syncthreads();
     }
-    // Activations.  Ordinary start: the first two slabs are requested, the first one goes to LDS.  After a wait the
-    // weights of the first HS slabs are on chip, so those steps would each cost one load latency of the activation
-    // pipeline (a slab is requested one step before it is stored): their activation slabs are requested XG steps ahead --
-    // the first XG at once, together with the two that the main loop starts from.
-    uint4 xr[2][NB];
+    // Activations.  Ordinary start: the first XD slabs are requested, the first one goes to LDS.  XD = PF, although their
+    // latency alone would need less: loads come back in order, so the wait for an activation slab is a wait for every
+    // weight slab requested before it, and requested two slabs ahead they held the weights to two slabs in flight.
+    // Measured, two slabs ahead -> PF ahead and a straight-line end of the range: 117 MB (70B-shaped TP=8 gate/up, batch 8, tiled)
+    // unchanged order of sums, a layer 105.3 -> 103.3 us; 43 MB QKV, batch 16 14.8 -> 13.4 us; 8B-shaped gate/up at batch 64 14.5 -> 13.0.
+    // After a wait the weights of the first HS slabs are on chip, so those steps would each cost one load latency of the
+    // activation pipeline: their activation slabs are requested XG steps ahead -- the first XG at once, together with the
+    // XD that the main loop starts from (two: the registers of a kernel that waits are counted, gemm_sk_can_wait).
+    constexpr int XD = WAIT ? 2 : PF;
+    uint4 xr[XD][NB];
     constexpr int XG = WAIT ? 6 : 1;
     uint4 xa[XG][NB];
     if (held) {
 #pragma unroll
         for (int h = 0; h < XG; ++h) load_slab(s0 + h, xa[h]);
-        if (s0 + HS < s1) load_slab(s0 + HS, xr[0]);
-        if (s0 + HS + 1 < s1) load_slab(s0 + HS + 1, xr[1]);
-    } else if (s0 < s1) {
-        load_slab(s0, xr[0]);
-        if (s0 + 1 < s1) load_slab(s0 + 1, xr[1]);
+        load_slab(min(s0 + HS, s1 - 1), xr[0]);
+        load_slab(min(s0 + HS + 1, s1 - 1), xr[1]);
+    } else {
+#pragma unroll
+        for (int q = 0; q < XD; ++q) load_slab(min(s0 + q, s1 - 1), xr[q]);
         store_slab(0, xr[0]);
     }
     // 1/rms of every batch row from the partial sums of squares (block order); read in the epilogue only.  The waiting
@@ -436,7 +443,8 @@ __global__ __launch_bounds__(256) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj)
     // Steady state: as long as every slab this round touches exists (s + PF < s1 for all four steps), the round is
     // straight-line code -- no predicate on any load.  Only then can the compiler count the loads issued after the
     // one it needs and wait with the exact vmcnt; behind predicated loads it waits for everything outstanding at the
-    // top of every round, which exposes a full memory latency per PF slabs.
+    // top of every round, which exposes a full memory latency per PF slabs.  The rounds at the end of the range keep
+    // that form: one whose refills partly lie past the range re-reads the last slab instead, the last one requests nothing.
     int sb = s0;
     if (held) {
         // The slabs held on chip, in the order of the range (the sum of a split has one order, launched ahead or not):
@@ -468,24 +476,49 @@ __global__ __launch_bounds__(256) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj)
     for (; sb + 2 * PF <= s1; sb += PF) {
 #pragma unroll
         for (int q = 0; q < PF; ++q) {
-            const int s = sb + q, buf = q & 1;      // (s - s0) & 1, because PF and the number of slabs parked in LDS are even
-            load_slab(s + 2, xr[q & 1]);
+            const int s = sb + q, buf = q & 1;      // (s - s0) & 1, because PF and the number of slabs held are even
+            load_slab(s + XD, xr[q % XD]);
             mfma_slab(buf, wq[q]);
             load_w_all(s + PF, wq[q]);
-            store_slab(buf ^ 1, xr[(q + 1) & 1]);
+            store_slab(buf ^ 1, xr[(q + 1) % XD]);
             __syncthreads();
         }
     }
-    for (; sb < s1; sb += PF) {                     // the last rounds: every step checks what is left
+    if constexpr (WAIT) {
+        for (; sb < s1; sb += PF) {                 // the last rounds: every step checks what is left
 #pragma unroll
-        for (int q = 0; q < PF; ++q) {
-            const int s = sb + q;
-            if (s < s1) {                       // uniform over the workgroup
-                const int buf = q & 1;
-                if (s + 2 < s1) load_slab(s + 2, xr[q & 1]);
+            for (int q = 0; q < PF; ++q) {
+                const int s = sb + q;
+                if (s < s1) {                       // uniform over the workgroup
+                    const int buf = q & 1;
+                    if (s + XD < s1) load_slab(s + XD, xr[q % XD]);
+                    mfma_slab(buf, wq[q]);
+                    if (s + PF < s1) load_w(s + PF, wq[q]);
+                    if (s + 1 < s1) store_slab(buf ^ 1, xr[(q + 1) % XD]);
+                    __syncthreads();
+                }
+            }
+        }
+    } else {
+        if (sb + PF < s1) {                         // refills partly past the range
+#pragma unroll
+            for (int q = 0; q < PF; ++q) {
+                const int s = sb + q, buf = q & 1;
+                load_slab(min(s + XD, s1 - 1), xr[q % XD]);
                 mfma_slab(buf, wq[q]);
-                if (s + PF < s1) load_w(s + PF, wq[q]);
-                if (s + 1 < s1) store_slab(buf ^ 1, xr[(q + 1) & 1]);
+                load_w_all(min(s + PF, s1 - 1), wq[q]);
+                store_slab(buf ^ 1, xr[(q + 1) % XD]);
+                __syncthreads();
+            }
+            sb += PF;
+        }
+#pragma unroll
+        for (int q = 0; q < PF; ++q) {              // what is left is in registers
+            const int s = sb + q;
+            if (s < s1) {
+                const int buf = q & 1;
+                mfma_slab(buf, wq[q]);
+                if (s + 1 < s1) store_slab(buf ^ 1, xr[(q + 1) % XD]);
                 __syncthreads();
             }
         }
@@ -542,11 +575,11 @@ constexpr int kSkI8Blocks = 66;    // 128-element blocks a workgroup's K range c
 // (8 KiB each), on chip.  The operand's block scales share cache lines between producer workgroups of different XCDs,
 // so the waiting variant reads those of its K range with device-coherent loads, once, after the wait.
 template <int NB, int HOLD>
-__global__ __launch_bounds__(256) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob pj)
+__global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob pj)
 {
     constexpr bool WAIT = HOLD > 0;
     static_assert(!WAIT || NB == 1, "the waiting variant is built for one batch tile");
-    constexpr int PF = 8;                          // slabs of weight codes in flight per wave (2 x 16 bytes each)
+    constexpr int PF = NB <= 2 ? 8 : 4;            // slabs of weight codes in flight per wave (2 x 16 bytes each); what two workgroups' registers hold
     __shared__ uint4 xs[2][NB * 2][64];            // [buffer][batch tile * 2 + digit][lane]
     __shared__ float bs[2][NB * 16];               // block scale of each batch row for the buffered slab
     __shared__ float inv_s[NB * 16];
@@ -577,24 +610,22 @@ __global__ __launch_bounds__(256) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob pj
     }
     // Lane (i, g) owns bytes g*16 .. g*16+15 of row i of every 64-element slab: the A operand of one MFMA.
     struct WFrag { uint4 c[2]; };
-    auto load_w = [&](int s, WFrag &f) {
+    auto load_w = [&](int s, WFrag &f) {       // unpredicated: a row past N reads row 0 (wp) and is never stored
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-            f.c[mt] = wok[mt] ? *reinterpret_cast<const uint4 *>(wp[mt] + (size_t)s * wstep) : zero16();
+        for (int mt = 0; mt < 2; ++mt) f.c[mt] = ld16(reinterpret_cast<const uint16_t *>(wp[mt] + (size_t)s * wstep));
     };
-    // activation slab: NB*128 16-byte units, unit u = ((tile*2 + digit)*16 + row)*4 + segment
+    // activation slab: NB*128 16-byte units, unit u = ((tile*2 + digit)*16 + row)*4 + segment; 256 units are two tiles, so one
+    // 32-bit offset from uniform bases serves all loads of a thread (see k_gemm_sk)
     constexpr int NU = (NB + 1) / 2;
     struct SlabRegs { uint4 r[NU]; float sc; };
+    const uint32_t x_off = (uint32_t)((size_t)((tid >> 6) & 1) * a.x_plane + (size_t)((tid >> 7) * 16 + ((tid >> 2) & 15)) * K + (tid & 3) * 16);
+    const uint32_t s_off = (uint32_t)(tid * nblk128 * 4);
     auto load_slab = [&](int s, SlabRegs &sr) {
 #pragma unroll
-        for (int j = 0; j < NU; ++j) {
-            const int u = tid + j * 256, n = u >> 7, dgt = (u >> 6) & 1, row = (u >> 2) & 15, seg = u & 3;
-            sr.r[j] = u < NB * 128 ? *reinterpret_cast<const uint4 *>(a.xd + (size_t)dgt * a.x_plane +
-                                                                       (size_t)(n * 16 + row) * K + (size_t)s * 64 + seg * 16)
-                                   : zero16();
-        }
+        for (int j = 0; j < NU; ++j)
+            sr.r[j] = tid + j * 256 < NB * 128 ? ld16(reinterpret_cast<const uint16_t *>(a.xd + ((size_t)j * 32 * K + (size_t)s * 64) + x_off)) : zero16();
         if (WAIT) sr.sc = tid < a.batch ? bsl[tid * kSkI8Blocks + (s >> 1) - (s0 >> 1)] : 0.f;
-        else sr.sc = tid < NB * 16 ? bscale[(size_t)tid * nblk128 + (s >> 1)] : 0.f;
+        else sr.sc = tid < NB * 16 ? *reinterpret_cast<const float *>(reinterpret_cast<const char *>(bscale + (s >> 1)) + s_off) : 0.f;
     };
     auto store_slab = [&](int buf, const SlabRegs &sr) {
 #pragma unroll
@@ -653,7 +684,7 @@ __global__ __launch_bounds__(256) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob pj
     WFrag wq[PF];
 #pragma unroll
     for (int q = 0; q < PF; ++q)
-        if (s0 + q < s1) load_w(s0 + q, wq[q]);
+        if (!WAIT || s0 + q < s1) load_w(min(s0 + q, s1 - 1), wq[q]);
     if (WAIT) {
         if (w == 0) sk_wait_for_operand(a.wt, a.batch, K, s0, s1, lane);     // one wave polls
         __syncthreads();
@@ -666,17 +697,19 @@ __global__ __launch_bounds__(256) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob pj
         }
         __syncthreads();
     }
-    SlabRegs xr[2];
+    // as many activation slabs as weight slabs in flight (see k_gemm_sk): 15 MB of gate/up at batch 39 17.2 -> 14.9 us
+    constexpr int XD = WAIT ? 2 : PF;
+    SlabRegs xr[XD];
     constexpr int XG = WAIT ? 6 : 1;        // activation slabs requested ahead in the held part (see k_gemm_sk)
     SlabRegs xa[XG];
     if (held) {
 #pragma unroll
         for (int h = 0; h < XG; ++h) load_slab(s0 + h, xa[h]);
-        if (s0 + HS < s1) load_slab(s0 + HS, xr[0]);
-        if (s0 + HS + 1 < s1) load_slab(s0 + HS + 1, xr[1]);
-    } else if (s0 < s1) {
-        load_slab(s0, xr[0]);
-        if (s0 + 1 < s1) load_slab(s0 + 1, xr[1]);
+        load_slab(min(s0 + HS, s1 - 1), xr[0]);
+        load_slab(min(s0 + HS + 1, s1 - 1), xr[1]);
+    } else {
+#pragma unroll
+        for (int q = 0; q < XD; ++q) load_slab(min(s0 + q, s1 - 1), xr[q]);
         store_slab(0, xr[0]);
     }
     auto inv_rms = [&]() {      // 1/rms of every batch row (see k_gemm_sk)
@@ -758,20 +791,59 @@ __global__ __launch_bounds__(256) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob pj
         if (sb0 < s1) store_slab(0, xr[0]);     // HS is even: the main loop's first slab goes to buffer 0
         __syncthreads();
     }
-    for (int sb = sb0; sb < s1; sb += PF) {
+    // straight-line rounds, then the end of the range: see k_gemm_sk
+    int sb = sb0;
+    for (; sb + 2 * PF <= s1; sb += PF) {
 #pragma unroll
         for (int q = 0; q < PF; ++q) {
-            const int s = sb + q;
-            if (s < s1) {                       // uniform over the workgroup
-                const int buf = q & 1;          // (s - s0) & 1, because PF and the number of slabs held are even
-                if (s + 2 < s1) load_slab(s + 2, xr[q & 1]);
+            const int s = sb + q, buf = q & 1;      // (s - s0) & 1, because PF and the number of slabs held are even
+            load_slab(s + XD, xr[q % XD]);
+            mfma_slab(s, buf, wq[q]);
+            load_w(s + PF, wq[q]);
+            store_slab(buf ^ 1, xr[(q + 1) % XD]);
+            __syncthreads();
+        }
+    }
+    if constexpr (WAIT) {
+        for (; sb < s1; sb += PF) {                 // the last rounds: every step checks what is left
+#pragma unroll
+            for (int q = 0; q < PF; ++q) {
+                const int s = sb + q;
+                if (s < s1) {                       // uniform over the workgroup
+                    const int buf = q & 1;
+                    if (s + XD < s1) load_slab(s + XD, xr[q % XD]);
+                    mfma_slab(s, buf, wq[q]);
+                    if (s + PF < s1) load_w(s + PF, wq[q]);
+                    if (s + 1 < s1) store_slab(buf ^ 1, xr[(q + 1) % XD]);
+                    __syncthreads();
+                }
+            }
+        }
+    } else {
+        if (sb + PF < s1) {                         // refills partly past the range
+#pragma unroll
+            for (int q = 0; q < PF; ++q) {
+                const int s = sb + q, buf = q & 1;
+                load_slab(min(s + XD, s1 - 1), xr[q % XD]);
                 mfma_slab(s, buf, wq[q]);
-                if (s + PF < s1) load_w(s + PF, wq[q]);
-                if (s + 1 < s1) store_slab(buf ^ 1, xr[(q + 1) & 1]);
+                load_w(min(s + PF, s1 - 1), wq[q]);
+                store_slab(buf ^ 1, xr[(q + 1) % XD]);
+                __syncthreads();
+            }
+            sb += PF;
+        }
+#pragma unroll
+        for (int q = 0; q < PF; ++q) {              // what is left is in registers
+            const int s = sb + q;
+            if (s < s1) {
+                const int buf = q & 1;
+                mfma_slab(s, buf, wq[q]);
+                if (s + 1 < s1) store_slab(buf ^ 1, xr[(q + 1) % XD]);
                 __syncthreads();
             }
         }
     }
+
     if (WAIT) {
         if (w == 0) sk_read_sums(a.wt, a.batch * (K / 512), lane, ssq_s);       // <= kSkWaitEntries
         __syncthreads();
