@@ -245,7 +245,11 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
     constexpr bool WAIT = HOLD > 0;
     static_assert(!WAIT || NB <= 2, "the waiting variant is built for one or two batch tiles");
     constexpr int PF = 4;   // slabs of weight fragments in flight per wave (8 measured slower: fewer straight-line rounds, more registers)
-    __shared__ uint4 xs[2][NB * 4][64];   // [buffer][(batch tile*2 + plane)*2 + k half][lane]
+    // [buffer][(batch tile*2 + plane)*2 + k half][lane].  Eight neighbouring threads hold the eight 16-byte segments of one batch
+    // row, whose fragment slots lie 256 bytes apart: all on the same banks.  Slot ^ segment spreads them over eight bank groups, and
+    // the 16 lanes of a read (one segment, 16 rows) still cover 256 contiguous bytes.
+    // Measured at batch 64: the 235 MB gate/up matrix 56.4 -> 50.0 us, 117 MB down 35.6 -> 32.7, 29 MB gate/up 13.0 -> 11.4.
+    __shared__ uint4 xs[2][NB * 4][64];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, i = lane & 15, g = lane >> 4;
     const int row_base = blockIdx.x * 128 + w * 32;
     const int s0 = blockIdx.y * a.slabs_per_block, s1 = min(s0 + a.slabs_per_block, a.n_slabs);
@@ -300,7 +304,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             const int u = tid + j * 256, n = u >> 8, p = (u >> 7) & 1, row = (u >> 3) & 15, seg = u & 7;
-            xs[buf][(n * 2 + p) * 2 + (seg >> 2)][(seg & 3) * 16 + row] = r[j];   // fragment order: k = half*32 + g*8 + e
+            // fragment order, k = half*32 + g*8 + e; the slot's lowest bits are swizzled with the segment, see xs
+            xs[buf][(n * 2 + p) * 2 + (seg >> 2)][((seg & 3) * 16 + row) ^ seg] = r[j];
         }
     };
 
@@ -372,8 +377,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
     // Activations.  Ordinary start: the first XD slabs are requested, the first one goes to LDS.  XD = PF, although their
     // latency alone would need less: loads come back in order, so the wait for an activation slab is a wait for every
     // weight slab requested before it, and requested two slabs ahead they held the weights to two slabs in flight.
-    // Measured, two slabs ahead -> PF ahead and a straight-line end of the range: 117 MB (70B-shaped TP=8 gate/up, batch 8, tiled)
-    // unchanged order of sums, a layer 105.3 -> 103.3 us; 43 MB QKV, batch 16 14.8 -> 13.4 us; 8B-shaped gate/up at batch 64 14.5 -> 13.0.
+    // Measured, two slabs ahead -> PF ahead and a straight-line end of the range: a 70B-shaped TP=8 layer at batch 8
+    // 105.3 -> 103.3 us; 43 MB QKV, batch 16 14.8 -> 13.4 us; 8B-shaped gate/up at batch 64 14.5 -> 13.0.
     // After a wait the weights of the first HS slabs are on chip, so those steps would each cost one load latency of the
     // activation pipeline: their activation slabs are requested XG steps ahead -- the first XG at once, together with the
     // XD that the main loop starts from (two: the registers of a kernel that waits are counted, gemm_sk_can_wait).
@@ -422,13 +427,14 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
     if (!WAIT) inv_rms();
     __syncthreads();
 
+    const int l0 = lane ^ g, l1 = lane ^ g ^ 4;        // this lane's slots of the two k halves
     auto mfma_slab = [&](int buf, const WFrag &f) {
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
-            const bf16x8 bh0 = __builtin_bit_cast(bf16x8, xs[buf][(n * 2 + 0) * 2 + 0][lane]);
-            const bf16x8 bh1 = __builtin_bit_cast(bf16x8, xs[buf][(n * 2 + 0) * 2 + 1][lane]);
-            const bf16x8 bl0 = __builtin_bit_cast(bf16x8, xs[buf][(n * 2 + 1) * 2 + 0][lane]);
-            const bf16x8 bl1 = __builtin_bit_cast(bf16x8, xs[buf][(n * 2 + 1) * 2 + 1][lane]);
+            const bf16x8 bh0 = __builtin_bit_cast(bf16x8, xs[buf][(n * 2 + 0) * 2 + 0][l0]);
+            const bf16x8 bh1 = __builtin_bit_cast(bf16x8, xs[buf][(n * 2 + 0) * 2 + 1][l1]);
+            const bf16x8 bl0 = __builtin_bit_cast(bf16x8, xs[buf][(n * 2 + 1) * 2 + 0][l0]);
+            const bf16x8 bl1 = __builtin_bit_cast(bf16x8, xs[buf][(n * 2 + 1) * 2 + 1][l1]);
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt) {
                 const bf16x8 a0 = __builtin_bit_cast(bf16x8, f.a0[mt]);
@@ -580,7 +586,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob
     constexpr bool WAIT = HOLD > 0;
     static_assert(!WAIT || NB == 1, "the waiting variant is built for one batch tile");
     constexpr int PF = NB <= 2 ? 8 : 4;            // slabs of weight codes in flight per wave (2 x 16 bytes each); what two workgroups' registers hold
-    __shared__ uint4 xs[2][NB * 2][64];            // [buffer][batch tile * 2 + digit][lane]
+    __shared__ uint4 xs[2][NB * 2][64];            // [buffer][batch tile * 2 + digit][lane ^ 2 * segment]: bank spread as in k_gemm_sk
     __shared__ float bs[2][NB * 16];               // block scale of each batch row for the buffered slab
     __shared__ float inv_s[NB * 16];
     __shared__ float bsl[WAIT ? 16 * kSkI8Blocks : 1];     // waiting variant: block scales of this K range, [batch row][block]
@@ -627,12 +633,11 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob
         if (WAIT) sr.sc = tid < a.batch ? bsl[tid * kSkI8Blocks + (s >> 1) - (s0 >> 1)] : 0.f;
         else sr.sc = tid < NB * 16 ? *reinterpret_cast<const float *>(reinterpret_cast<const char *>(bscale + (s >> 1)) + s_off) : 0.f;
     };
+    const int x_slot = ((tid & 3) * 16 + ((tid >> 2) & 15)) ^ (2 * (tid & 3)), x_frag = (tid >> 7) * 2 + ((tid >> 6) & 1);
     auto store_slab = [&](int buf, const SlabRegs &sr) {
 #pragma unroll
-        for (int j = 0; j < NU; ++j) {
-            const int u = tid + j * 256, n = u >> 7, dgt = (u >> 6) & 1, row = (u >> 2) & 15, seg = u & 3;
-            if (u < NB * 128) xs[buf][n * 2 + dgt][seg * 16 + row] = sr.r[j];   // B operand: lane (row, segment)
-        }
+        for (int j = 0; j < NU; ++j)
+            if (tid + j * 256 < NB * 128) xs[buf][j * 4 + x_frag][x_slot] = sr.r[j];   // B operand: lane (row, segment)
         if (tid < NB * 16) bs[buf][tid] = sr.sc;
     };
     f32x4 acc[2][NB];
@@ -743,12 +748,13 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob
 
     // one slab: both digit planes against the weight codes; at the end of a 128-element block (or of the range) the pair
     // of exact sums is folded into the fp32 accumulator
+    const int x_lane = lane ^ (2 * g);
     auto mfma_slab = [&](int s, int buf, const WFrag &f) {
         const bool fold = (s & 1) || s + 1 == s1;
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
-            const i32x4 x1 = __builtin_bit_cast(i32x4, xs[buf][n * 2 + 0][lane]);
-            const i32x4 x2 = __builtin_bit_cast(i32x4, xs[buf][n * 2 + 1][lane]);
+            const i32x4 x1 = __builtin_bit_cast(i32x4, xs[buf][n * 2 + 0][x_lane]);
+            const i32x4 x2 = __builtin_bit_cast(i32x4, xs[buf][n * 2 + 1][x_lane]);
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt) {
                 const i32x4 wc = __builtin_bit_cast(i32x4, f.c[mt]);
