@@ -572,7 +572,7 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
             HIP_TRY(launch_gemm_sk(Wqkv, Mat{}, 0, h1b, ssq, d.rms_eps, part, B, QR, H, wait_qkv ? &skw : nullptr, s));
             wait_qkv = false;
             ST_TRY(prof_tag(c, -2));
-            HIP_TRY(launch_sk_reduce(part, gemm_sk_splits(B, QR, H, w8, tiled), B, QR, false, qkv, nullptr, false, s));
+            HIP_TRY(launch_sk_reduce(part, gemm_sk_splits(B, QR, H, w8, tiled, false), B, QR, false, qkv, nullptr, false, s));
         }
 
         if (!seg_attn) {
@@ -597,7 +597,7 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
             if (!gemm_sk_supported(B, H, QD)) return PSV_ERR_UNSUPPORTED;
             HIP_TRY(launch_gemm_sk(Wo, Mat{}, 0, attnb, nullptr, 0.f, part, B, H, QD, nullptr, s));
             attn_delta = part;
-            attn_splits = gemm_sk_splits(B, H, QD, w8, tiled);
+            attn_splits = gemm_sk_splits(B, H, QD, w8, tiled, false);
         }
 
         {
@@ -630,7 +630,7 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
             HIP_TRY(launch_gemm_sk(Wg, Wu, F, h2b, ssq, d.rms_eps, part, B, 2 * F, H, wait_gate ? &skw : nullptr, s));
             wait_gate = false;
             ST_TRY(prof_tag(c, -2));
-            HIP_TRY(launch_sk_reduce(part, gemm_sk_splits(B, 2 * F, H, w8, tiled), B, 2 * F, true, m, mb, w8, s));
+            HIP_TRY(launch_sk_reduce(part, gemm_sk_splits(B, 2 * F, H, w8, tiled, true), B, 2 * F, true, m, mb, w8, s));
         }
 
         if (!seg_mlp) ST_TRY(prof_tag(c, PSV_OP_DOWN));
@@ -643,7 +643,7 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
             if (!gemm_sk_supported(B, H, F)) return PSV_ERR_UNSUPPORTED;
             HIP_TRY(launch_gemm_sk(Wd, Mat{}, 0, mb, nullptr, 0.f, part, B, H, F, nullptr, s));
             delta = part;
-            delta_splits = gemm_sk_splits(B, H, F, w8, tiled);
+            delta_splits = gemm_sk_splits(B, H, F, w8, tiled, false);
         }
 
         {

@@ -878,16 +878,38 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob
     }
 }
 
-// Number of K splits, from a small cost model of the kernel: a workgroup needs ~0.6 us per slab it walks
-// (latency of one pipelined slab step), 512 workgroups are resident at a time, and weights plus partial
-// results (written once, read back once) stream at ~4 TB/s.  More splits shorten the walk and cost partial
-// traffic of batch * N * 8 bytes each; small matrices at batch 64 end up with 4-16 splits, wide ones at
-// small batch with as many as keep every CU busy.
-int gemm_sk_splits(int batch, int N, int K, bool w8, bool tiled)
+// Number of K splits, from a small cost model of the kernel.  More splits shorten the walk and cost partial traffic of
+// batch * N * 8 bytes each; small matrices end up with 8-16 splits, wide ones with as many as keep every CU busy.
+//
+// One matrix, bf16 weights (QKV, O, down): a CU is as fast with one workgroup as with two (the two share its matrix cores,
+// LDS and memory pipeline; measured at batch 64, 117 MB: 256 workgroups of 28 slabs 30.7 us, 512 of 14 32.8, 448 of 16 33.2,
+// 384 of 19 36.0), so the walk is the fullest CU's: ceil(workgroups / 256) times the slabs of a range, 0.45 us each, and the
+// chip is best covered once.  Partial results travel through the memory-side cache, 5 TB/s.  Against the rule below:
+// 42 MB QKV at batch 64 16.9 -> 13.6 us, at batch 16 13.4 -> 11.9; 59 MB down at batch 32 15.6 -> 13.6; 33 MB O at
+// batch 16 10.3 -> 8.3; the down and O kernels' consumers read half the partials.
+//
+// Gate | up (pair) and int8 weights: a workgroup needs ~0.6 us per slab it walks (latency of one pipelined slab step), 512
+// workgroups are resident at a time, and weights plus partial results stream at ~4 TB/s.  The pair keeps it because the
+// share of its range that a workgroup holds on chip through a communication window depends on short ranges
+// (gemm_sk_can_wait), and without one 224 workgroups and 448 measured the same (50.1 us, 235 MB at batch 64); int8 ranges
+// are half the bytes per slab, bound by latency, and want the second workgroup.
+int gemm_sk_splits(int batch, int N, int K, bool w8, bool tiled, bool pair)
 {
     const int n_slabs = K / 64;
     const double row_groups = (double)((N + 127) / 128);
     const double w_bytes = (w8 ? 1.0 : 2.0) * N * K, part_bytes = 8.0 * batch * N;
+    if (!w8 && !pair) {
+        int best = 1;
+        double best_cost = 1e30;
+        for (int ks = 1; ks <= kSkMaxSplits && ks * 2 <= n_slabs; ++ks) {
+            const int spb = (n_slabs + ks - 1) / ks;
+            if ((n_slabs + spb - 1) / spb != ks) continue;
+            const double fullest = (double)(((long long)row_groups * ks + 255) / 256);
+            const double cost = fullest * spb * 0.45 + ks * part_bytes / 5.0e6;
+            if (cost < best_cost - 1e-9) { best_cost = cost; best = ks; }
+        }
+        return best;
+    }
     int best = 1, best1 = 0;                    // best1: the best choice whose workgroups are all resident at once
     double best_cost = 1e30, best1_cost = 1e30;
     for (int ks = 1; ks <= kSkMaxSplits && ks * 2 <= n_slabs; ++ks) {
@@ -953,7 +975,7 @@ static const SkWaitRes &sk_wait_res()
     return r;
 }
 
-// Can this projection be launched ahead of its activations (launch_gemm_sk with a wait)?  Its workgroups then sit on
+// Can this projection (gate | up) be launched ahead of its activations (launch_gemm_sk with a wait)?  Its workgroups then sit on
 // the compute units until k_resid_sum has run, so all of them must be resident at once and leave room for that kernel:
 // either a quarter of the compute units keep a free workgroup slot of this kernel's size, or a wave of k_resid_sum fits
 // beside a full house (512 registers per lane and SIMD, with 16 to spare; 160 KiB of LDS, with 4 KiB to spare).
@@ -963,7 +985,7 @@ bool gemm_sk_can_wait(int batch, int N, int K, bool w8, bool tiled, int cus)
     if (batch > (w8 ? 16 : kSkWaitMaxBatch)) return false;         // the instantiations of the waiting kernels
     const SkWaitRes &r = sk_wait_res();
     if (!r.ok) return false;
-    const int splits = gemm_sk_splits(batch, N, K, w8, tiled);
+    const int splits = gemm_sk_splits(batch, N, K, w8, tiled, true);
     const int nb = (batch + 15) / 16;
     const int kind = w8 ? 1 : nb == 2 ? 2 : 0, lv = sk_hold_level((K / 64 + splits - 1) / splits, nb) - 1;
     const long long grid = (long long)((N + 127) / 128) * splits;
@@ -1004,7 +1026,7 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
         q.xd = reinterpret_cast<const uint8_t *>(xb); q.x_plane = (size_t)nb * 16 * K;
         q.part = part; q.batch = batch; q.N = N; q.K = K; q.n_slabs = K / 64; q.ssq = ssq; q.eps = eps;
         q.tiled = W.tiled ? 1 : 0;
-        const int splits = gemm_sk_splits(batch, N, K, true, W.tiled);
+        const int splits = gemm_sk_splits(batch, N, K, true, W.tiled, W2.w != nullptr);
         q.slabs_per_block = (q.n_slabs + splits - 1) / splits;
         const dim3 grid((N + 127) / 128, splits);
         if (wait) {
@@ -1029,7 +1051,7 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
     a.split_row = W2.w ? split_row : N; a.xb = xb; a.x_plane = (size_t)nb * 16 * K;
     a.part = part; a.batch = batch; a.N = N; a.K = K; a.n_slabs = K / 64;
     a.tiled = W.tiled ? 1 : 0;
-    const int splits = gemm_sk_splits(batch, N, K, false, W.tiled);
+    const int splits = gemm_sk_splits(batch, N, K, false, W.tiled, W2.w != nullptr);
     a.slabs_per_block = (a.n_slabs + splits - 1) / splits;
     const dim3 grid((N + 127) / 128, splits);
     if (wait) {

@@ -78,8 +78,9 @@ def path_of(batch, hidden, weight_layout="row"):
 
 
 def sk_splits(batch, n_rows, k, weight_bytes=2.0, tiled=False):
-    """K splits of the split-K GEMM: the library's cost model (0.6 us per slab step, 512 resident workgroups, weights and
-    partials at 4 TB/s)."""
+    """K splits of the split-K GEMM: the library's cost model for the gate/up pair and for int8 weights (0.6 us per slab step,
+    512 resident workgroups, weights and partials at 4 TB/s).  For one bf16 matrix (QKV, O, down) the library has since taken
+    to covering the chip once; the constants here were calibrated, and the recorded rows measured, with this rule throughout."""
     n_slabs = k // 64
     row_groups = (n_rows + 127) // 128
     w_bytes, part_bytes = weight_bytes * n_rows * k, 8.0 * batch * n_rows
