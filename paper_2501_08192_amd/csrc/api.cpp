@@ -286,7 +286,7 @@ psv_status psv_tune_attention(psv_ctx *c, const float *x_in, float *x_out, uint3
         if (n_chunks > (uint64_t)kAttnMaxChunks || (k >= 0 && chunk == (uint32_t)def.chunk_tokens)) continue;
         const uint64_t wgs = n_chunks * d.n_kv_heads * batch;
         if (k >= 0 && (wgs > 8192 || (wgs < 128 && chunk > unit))) continue;   // far from filling the chip, or a long tail of rounds
-        c->attn_chunk_tokens = chunk;
+        c->attn_chunk_tokens = k < 0 ? 0 : chunk;      // 0: what a context runs that keeps the default
         float ms = 0.f;
         for (int rep = 0; rep < 2 + 8 && st == PSV_OK; ++rep) {
             if (rep == 2 && hipEventRecord(e0, c->main) != hipSuccess) st = PSV_ERR_HIP;

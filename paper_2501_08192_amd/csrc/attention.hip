@@ -4,19 +4,79 @@
 // is bound by HBM bandwidth (Section 2, "LLM decoding is memory BW-limited"), so the kernels are built around
 // 16-byte-per-lane coalesced loads with many loads in flight per 64-lane wave; the matrix cores are used where a
 // vector-ALU formulation would bind on arithmetic (batch > 2 projections, grouped-query attention).
+#include <type_traits>
+
 #include "device.h"
 
 namespace psv {
 
 // ------------------------------------------------------------------------------------ RoPE table
 
+// Attention span of a sequence; a length outside the descriptor's range is treated as an empty sequence.
+__device__ __forceinline__ int attn_span(int T, int max_tokens) { return T < 0 || T > max_tokens ? 0 : T; }
+
+constexpr unsigned kAttnLast = 1u << 31;        // in AttnPlan::map: the sequence's last chunk
+
+// Attention's work list of a step (AttnPlan), made by one wave with a lane per sequence (batch <= 64).  The chunk size is the
+// smallest number of units with which the chunks of all sequences fit the slots.
+__device__ __forceinline__ void make_attn_plan(const int32_t *seq_lens, int max_tokens, int batch, const AttnPlan &p, int lane)
+{
+    const int T = lane < batch ? attn_span(seq_lens[lane], max_tokens) : 0;
+    const int units = (T + p.unit - 1) / p.unit;
+    int n = 0;
+    auto total = [&](int c) {
+        n = (units + c - 1) / c;
+        return (int)wave_sum((float)n);                 // exact: far below 2^24
+    };
+    const int all = (int)wave_sum((float)units);
+    int lo = max((p.max_units + kAttnMaxChunks - 1) / kAttnMaxChunks, (all + p.slots - 1) / p.slots);
+    if (lo < 1) lo = 1;
+    if (total(lo) > p.slots) {                          // binary search: fewer chunks with larger sizes, and max_units always fits
+        int hi = p.max_units;
+        ++lo;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (total(mid) <= p.slots) hi = mid;
+            else lo = mid + 1;
+        }
+        (void)total(lo);
+    }
+    if (lane < batch) p.chunks[lane] = n;
+    int v = n;                                          // inclusive scan: within rows of 16, then the rows before
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    const int r0 = __builtin_amdgcn_readlane(v, 15), r1 = __builtin_amdgcn_readlane(v, 31), r2 = __builtin_amdgcn_readlane(v, 47);
+    const int row = lane >> 4, start = v - n + (row > 0 ? r0 : 0) + (row > 1 ? r1 : 0) + (row > 2 ? r2 : 0);
+    const int at = __builtin_amdgcn_readlane(start + n, 63);
+    const int chunk = lo * p.unit;
+    auto put = [&](int k, int b, int c, int nb, int Tb) {
+        p.map[k] = make_uint2((unsigned)b << 24 | (unsigned)c << 12 | (unsigned)lo, (unsigned)min(Tb, (c + 1) * chunk) | (c == nb - 1 ? kAttnLast : 0u));
+    };
+    if (wave_max((float)n) < 2.f * batch) {             // a lane writes its sequence's chunks; long sequences: the wave, one by one
+        for (int c = 0; c < n; ++c) put(start + c, lane, c, n, T);
+    } else {
+        for (int b = 0; b < batch; ++b) {
+            const int nb = __builtin_amdgcn_readlane(n, b), sb = __builtin_amdgcn_readlane(start, b), Tb = __builtin_amdgcn_readlane(T, b);
+            for (int c = lane; c < nb; c += 64) put(sb + c, b, c, nb, Tb);
+        }
+    }
+    for (int k = at + lane; k < p.slots; k += 64) p.map[k] = make_uint2(0u, 0u);       // nothing to do
+}
+
 // cos/sin of the rotary angles at position seq_len-1, one row of 64 pairs per sequence.  The angle
 // is formed and reduced in double (position * theta^(-2i/128)), so long contexts lose nothing to
-// fp32 range reduction.  The position is the same for every layer, so this runs once per step.
+// fp32 range reduction.  The position is the same for every layer, so this runs once per step -- as does the plan of the
+// attention's work, by one more workgroup (blockIdx.x == batch).
 __global__ __launch_bounds__(64) void k_rope_table(const int32_t *__restrict__ seq_lens, const double *__restrict__ inv_freq,
-                                                   int max_tokens, float2 *__restrict__ table)
+                                                   int max_tokens, int batch, float2 *__restrict__ table, AttnPlan plan)
 {
     const int b = blockIdx.x, i = threadIdx.x;
+    if (b == batch) {
+        make_attn_plan(seq_lens, max_tokens, batch, plan, i);
+        return;
+    }
     int T = seq_lens[b];
     if (T < 1 || T > max_tokens) T = 1;
     float2 cs = make_float2(1.f, 0.f);
@@ -29,13 +89,16 @@ __global__ __launch_bounds__(64) void k_rope_table(const int32_t *__restrict__ s
 }
 
 hipError_t launch_rope_table(const int32_t *seq_lens, const double *inv_freq, int max_tokens, int batch, float2 *table,
-                             hipStream_t s)
+                             const AttnPlan *plan, hipStream_t s)
 {
-    PSV_LAUNCH(k_rope_table, dim3(batch), dim3(64), 0, s, seq_lens, inv_freq, max_tokens, table);
+    if (plan && (batch > 64 || plan->slots < batch)) return hipErrorInvalidValue;
+    PSV_LAUNCH(k_rope_table, dim3(batch + (plan ? 1 : 0)), dim3(64), 0, s, seq_lens, inv_freq, max_tokens, batch, table, plan ? *plan : AttnPlan{});
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------ decode attention
+
+constexpr float kAttnScale = 0.08838834764831845f * 1.4426950408889634f;   // 1/sqrt(128) * log2(e)
 
 AttnSplit attn_split(uint32_t batch, uint32_t n_kv_heads, uint32_t max_seq, bool kv_int8)
 {
@@ -59,8 +122,32 @@ AttnSplit attn_split(uint32_t batch, uint32_t n_kv_heads, uint32_t max_seq, bool
     return sp;
 }
 
+// The split above divides the longest possible sequence: in a batch of mixed lengths most of its workgroups are empty and the
+// longest sequence's chunks decide, and so it is for lengths far below max_seq.  A plan divides the lengths of the step, for
+// the same one resident round of workgroups: as many slots per kv head, filled by the smallest chunk size that fits
+// (make_attn_plan, once a step); a workgroup reads its chunk from its slot, a sequence's partials lie where its longest
+// possible number of chunks would put them.  Measured: 39 sequences of 375-6000 tokens, int8 cache, 31.0 -> 15.9 us a layer.
+bool attn_plan(uint32_t batch, uint32_t n_kv_heads, uint32_t max_seq, bool kv_int8, uint2 *map, size_t map_bytes, int *chunks, AttnPlan *p)
+{
+    p->unit = (kv_int8 ? kAttnTileTokensInt8 : kAttnTileTokens) * kAttnWaves;
+    p->max_units = (int)(((uint64_t)max_seq + p->unit - 1) / p->unit);
+    p->max_chunks = p->max_units < kAttnMaxChunks ? p->max_units : kAttnMaxChunks;
+    uint64_t slots = kAttnResident / n_kv_heads;
+    if (slots < batch) slots = batch;                               // every sequence needs one
+    const uint64_t finest = (uint64_t)batch * p->max_chunks;
+    p->slots = (int)(slots < finest ? slots : finest);
+    p->map = map;
+    p->chunks = chunks;
+    // an entry holds a sequence in 8 bits, chunk and chunk size in 12 each
+    return batch <= 64 && p->max_units < 4096 && p->slots * sizeof(uint2) <= map_bytes;
+}
+
 struct AttnArgs {
     const float *qkv;          // [batch][(nq+2nkv)*128] projection output, not yet rotated
+    const uint8_t *q;          // prepared queries (k_attn_prep)
+    int appended;              // ... which has also appended the new rows
+    int batch;
+    AttnPlan plan;             // plan.map null: chunks of chunk_tokens, n_chunks a sequence
     const float2 *rope;        // [batch][64] (cos, sin)
     KvView kv;
     int nq, nkv, chunk_tokens, n_chunks;
@@ -72,12 +159,180 @@ struct AttnArgs {
     int out_digits;            // out_bf16 receives int8 digit planes (operand of an int8 projection) instead
 };
 
+// Prepares the attention of a layer from the split-K partials of its QKV projection: sums them (split order), rotates queries
+// and new key, leaves the queries as the attention's matrix operands (two bf16 planes [batch][nq * 128], or for an int8 cache
+// two digit planes and a scale per head) and appends key and value to the cache.  A lane holds V channels and their rotary
+// partners, 64 / V lanes a row of 128; all splits are requested at once.  Bound by its launch and one round
+// trip.  What it takes out of the attention kernel stood there in every wave of every chunk, and in the workgroup of the last
+// chunk as a second load of the tile with the new rows.
+struct AttnPrepArgs {
+    const float *part;          // [splits][batch][(nq + 2 nkv) * 128]
+    int splits;
+    const float2 *rope;
+    KvView kv;
+    int batch, nq, nkv;
+    float *qkv;                 // the sums, [batch][(nq + 2 nkv) * 128]
+    uint8_t *q;
+};
+template <bool Q8, int V, bool APPEND>
+__global__ __launch_bounds__(64) void k_attn_prep(AttnPrepArgs a)
+{
+    constexpr int LANES = 64 / V;
+    using Vec = typename std::conditional<V == 2, float2, float4>::type;
+    const int lane = threadIdx.x % LANES, f = lane * V, nr = a.nq + 2 * a.nkv, nq = a.nq;
+    const int row = blockIdx.x * V + threadIdx.x / LANES;
+    const bool live = row < a.batch * nr;
+    const int b = live ? row / nr : 0, j = live ? row % nr : 0;
+    const size_t at = ((size_t)b * nr + j) * 128 + f, stride = (size_t)a.batch * nr * 128;
+    union Piece { Vec v; float e[V]; };
+    Piece lo[kSkMaxSplits], hi[kSkMaxSplits];
+#pragma unroll
+    for (int ks = 0; ks < kSkMaxSplits; ++ks) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) lo[ks].e[e] = hi[ks].e[e] = 0.f;
+        if (ks < a.splits) {
+            lo[ks].v = *reinterpret_cast<const Vec *>(a.part + ks * stride + at);
+            hi[ks].v = *reinterpret_cast<const Vec *>(a.part + ks * stride + at + 64);
+        }
+    }
+    float2 cs[V];
+#pragma unroll
+    for (int e = 0; e < V; e += 2) *reinterpret_cast<float4 *>(cs + e) = *reinterpret_cast<const float4 *>(a.rope + b * 64 + f + e);
+    // the new token's place, for the rows that go to the cache
+    const KvView &kv = a.kv;
+    const int T = APPEND ? attn_span(kv.seq_lens[b], kv.max_tokens) : 0, r = (T - 1) & 15;
+    const bool key = j < nq + a.nkv;
+    const int blk = live && j >= nq && T >= 1 ? kv_phys_block(kv.page_table, kv.max_blocks, kv.num_pool_blocks, b, (T - 1) >> 4) : -1;
+    const int kvh = key ? j - nq : j - nq - a.nkv;
+    Piece l = lo[0], h = hi[0];
+#pragma unroll
+    for (int ks = 1; ks < kSkMaxSplits; ++ks)
+#pragma unroll
+        for (int e = 0; e < V; ++e) { l.e[e] += lo[ks].e[e]; h.e[e] += hi[ks].e[e]; }
+    if (live) {
+        *reinterpret_cast<Vec *>(a.qkv + at) = l.v;
+        *reinterpret_cast<Vec *>(a.qkv + at + 64) = h.v;
+    }
+    if (key) {          // queries and the key are rotated
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            const float l0 = l.e[e], h0 = h.e[e];
+            l.e[e] = l0 * cs[e].x - h0 * cs[e].y;
+            h.e[e] = h0 * cs[e].x + l0 * cs[e].y;
+        }
+    }
+    const size_t plane = (size_t)a.batch * nq * 128, qat = ((size_t)b * nq + j) * 128 + f;
+    if constexpr (Q8) {
+        static_assert(V == 2, "a head is half a wave");
+        const float amax = max32(fmaxf(fmaxf(fabsf(l.e[0]), fabsf(l.e[1])), fmaxf(fabsf(h.e[0]), fabsf(h.e[1]))));
+        if (j >= nq) {
+            if (blk < 0) return;
+            const float sc = amax > 0.f ? amax / 127.0f : 1.0f;
+            uint8_t *d = reinterpret_cast<uint8_t *>(key ? kv.k_pool : kv.v_pool) + ((size_t)blk * a.nkv + kvh) * PSV_KV_UNIT_BYTES_INT8;
+            const int at8 = key ? r * 128 + f : f * 16 + r, step = key ? 1 : 16, far = key ? 64 : 64 * 16;
+            d[at8] = quant_i8(l.e[0], sc);
+            d[at8 + step] = quant_i8(l.e[1], sc);
+            d[at8 + far] = quant_i8(h.e[0], sc);
+            d[at8 + far + step] = quant_i8(h.e[1], sc);
+            if (lane == 0) reinterpret_cast<float *>(d + 2048)[r] = sc;
+            return;
+        }
+        if (!live) return;
+        const float inv = amax > 0.f ? 127.0f / amax : 0.f;
+        float d1[4], d2[4];
+        two_digits(l.e[0] * inv, d1[0], d2[0]);
+        two_digits(l.e[1] * inv, d1[1], d2[1]);
+        two_digits(h.e[0] * inv, d1[2], d2[2]);
+        two_digits(h.e[1] * inv, d1[3], d2[3]);
+        const uint32_t w1 = pack_magic_bytes(d1[0], d1[1], d1[2], d1[3]), w2 = pack_magic_bytes(d2[0], d2[1], d2[2], d2[3]);
+        *reinterpret_cast<uint16_t *>(a.q + qat) = (uint16_t)w1;
+        *reinterpret_cast<uint16_t *>(a.q + qat + 64) = (uint16_t)(w1 >> 16);
+        *reinterpret_cast<uint16_t *>(a.q + plane + qat) = (uint16_t)w2;
+        *reinterpret_cast<uint16_t *>(a.q + plane + qat + 64) = (uint16_t)(w2 >> 16);
+        if (lane == 0) reinterpret_cast<float *>(a.q + 2 * plane)[b * nq + j] = amax / 127.0f / 254.0f * kAttnScale;
+    } else {
+        if (j >= nq) {
+            if (blk < 0) return;
+            const bool tm = kv.token_major;
+            uint16_t *d = key ? kv.k_pool : kv.v_pool;
+            if (tm || key) d += (tm ? (((size_t)blk * 16 + r) * a.nkv + kvh) * 128 : (((size_t)blk * a.nkv + kvh) * 16 + r) * 128) + f;
+            else d += (((size_t)blk * a.nkv + kvh) * 128 + f) * 16 + r;
+            const int step = tm || key ? 1 : 16;
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                d[e * step] = (uint16_t)f32_to_bf16(l.e[e]);
+                d[(64 + e) * step] = (uint16_t)f32_to_bf16(h.e[e]);
+            }
+            return;
+        }
+        if (!live) return;
+        uint16_t *q = reinterpret_cast<uint16_t *>(a.q) + qat;
+        uint32_t wl[V / 2], wll[V / 2], wh[V / 2], whl[V / 2];
+#pragma unroll
+        for (int e = 0; e < V / 2; ++e) {
+            pack_split(l.e[2 * e], l.e[2 * e + 1], wl[e], wll[e]);
+            pack_split(h.e[2 * e], h.e[2 * e + 1], wh[e], whl[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < V / 2; ++e) {
+            reinterpret_cast<uint32_t *>(q)[e] = wl[e];
+            reinterpret_cast<uint32_t *>(q + 64)[e] = wh[e];
+            reinterpret_cast<uint32_t *>(q + plane)[e] = wll[e];
+            reinterpret_cast<uint32_t *>(q + plane + 64)[e] = whl[e];
+        }
+    }
+}
+
+// Who appends: this kernel, which has the rows at hand; but its end waits for the value rows' 2-byte stores, one into every
+// channel, so that from batch 17 on a bf16 cache's rows are left to the attention, which has the time for them (70B-shaped
+// TP=8, batch 32, 32k tokens: 854 -> 847 us for four layers; TP=4, batch 64: 788 -> 778; batch 5 and 8 the other way round,
+// 643 / 637).  The larger batch also takes pieces of four channels: half the waves.
+static bool prep_appends(const KvView &kv, int batch) { return kv.int8 || batch <= 16; }
+
+hipError_t launch_attn_prep(const float *part, int splits, const float2 *rope, KvView kv, int batch, int nq, int nkv, float *qkv,
+                            void *q, hipStream_t s)
+{
+    if (splits < 1 || splits > kSkMaxSplits) return hipErrorInvalidValue;
+    const AttnPrepArgs a{part, splits, rope, kv, batch, nq, nkv, qkv, static_cast<uint8_t *>(q)};
+    const unsigned n_rows = (unsigned)(batch * (nq + 2 * nkv));
+    if (kv.int8) PSV_LAUNCH((k_attn_prep<true, 2, true>), dim3((n_rows + 1) / 2), dim3(64), 0, s, a);
+    else if (prep_appends(kv, batch)) PSV_LAUNCH((k_attn_prep<false, 2, true>), dim3((n_rows + 1) / 2), dim3(64), 0, s, a);
+    else PSV_LAUNCH((k_attn_prep<false, 4, false>), dim3((n_rows + 3) / 4), dim3(64), 0, s, a);
+    return hipGetLastError();
+}
+
+// What a workgroup works on: chunk c of sequence b, tokens [t_begin, t_end); its partial's place.
+struct AttnChunk { int b, t_begin, t_end; bool last; size_t slot; };     // last: it holds the new token, t_end - 1
+template <bool PREP>
+__device__ __forceinline__ AttnChunk attn_chunk(const AttnArgs &a, int kvh)
+{
+    AttnChunk k;
+    if (PREP && a.plan.map) {
+        const uint2 m = a.plan.map[blockIdx.x];     // the same for the whole grid column: a scalar load
+        const int c = (int)(m.x >> 12 & 0xfffu);
+        k.b = (int)(m.x >> 24);
+        k.t_begin = c * (int)(m.x & 0xfffu) * a.plan.unit;
+        k.t_end = (int)(m.y & ~kAttnLast);
+        k.last = m.y & kAttnLast;
+        k.slot = ((size_t)k.b * a.nkv + kvh) * a.plan.max_chunks + c;
+    } else {
+        k.b = blockIdx.z;
+        const int T = attn_span(a.kv.seq_lens[k.b], a.kv.max_tokens);
+        k.t_begin = blockIdx.x * a.chunk_tokens;
+        k.t_end = min(T, k.t_begin + a.chunk_tokens);
+        k.last = T >= 1 && (int)blockIdx.x == (T - 1) / a.chunk_tokens;
+        k.slot = ((size_t)k.b * a.nkv + kvh) * a.n_chunks + blockIdx.x;
+    }
+    return k;
+}
+
 // Split-K decode attention with everything around it fused in.  grid (chunks, kv heads, batch),
 // 4 waves; wave w of chunk c takes the 32-token tiles c*chunk + (w + 4*it)*32.
 //
 //  * prologue: the G <= 16 query heads sharing the kv head are rotated (RoPE) straight into MFMA
 //    B-fragments; the workgroup whose chunk holds token T-1 also rotates the new key, rounds key and
-//    value to bf16 and appends them to the cache before it reads its tiles.
+//    value to bf16, appends them to the cache and puts them into the tile it has already requested.
+//    PREP: k_attn_prep has left the queries as fragments and, for small batches, appended the rows.
 //  * main loop: all G heads ride in the N side of the MFMAs, so K and V are read from HBM once.
 //        S^T[token][g]  = K[token][:] . Q[g][:]          A = K rows (token-major in the pool)
 //        O^T[chan][g]  += V^T[chan][token] P[g][token]   A = V^T rows (channel-major in the pool)
@@ -93,21 +348,22 @@ struct AttnArgs {
 // needs, per lane, eight consecutive tokens of one channel: each wave passes its 32 x 128 tile through LDS (whole
 // 256-byte token rows in, 16-byte pieces XOR-swizzled by the token's group of eight so that the transposed 2-byte
 // reads of all 64 lanes fall into different banks) and picks its fragments up transposed.
-template <bool TM>
-__global__ __launch_bounds__(256) void k_attn(AttnArgs a)
+template <bool TM, bool PREP>
+__global__ __launch_bounds__(256, PREP ? 2 : 1) void k_attn(AttnArgs a)
 {
+    __shared__ __align__(16) uint16_t fresh[2][128];      // the new key and value row
     __shared__ float ms[kAttnWaves][16], ls[kAttnWaves][16];
     __shared__ f32x4 accs[kAttnWaves][8][64];      // TM: also the waves' value tiles (4 x 8 KiB) while the loop runs
 
-    const int b = blockIdx.z, kvh = blockIdx.y, c = blockIdx.x;
+    const int kvh = blockIdx.y;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, i = lane & 15, q4 = lane >> 4;
     const int nq = a.nq, nkv = a.nkv, G = nq / nkv;
     const KvView &kv = a.kv;
     const int qkv_rows = (nq + 2 * nkv) * 128;
-    int T = kv.seq_lens[b];
-    if (T < 0 || T > kv.max_tokens) T = 0;      // a length outside the descriptor's range is treated as an empty sequence
-    const int t_begin = c * a.chunk_tokens;
-    const int t_end = min(T, t_begin + a.chunk_tokens);
+    const AttnChunk ch = attn_chunk<PREP>(a, kvh);
+    const bool planned = PREP && a.plan.map;
+    if (planned && ch.t_end == 0) return;      // no chunk left for this workgroup
+    const int b = ch.b, t_begin = ch.t_begin, t_end = ch.t_end;
     const float *qkv_b = a.qkv + (size_t)b * qkv_rows;
     const float2 *rope_b = a.rope + b * 64;
 
@@ -170,12 +426,21 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a)
     // table, then the tile itself.  Loads return in order, so the query can be rotated while the tile -- the one
     // request that goes all the way to HBM -- is still on its way.
     const int t_first = t_begin + w * kAttnTileTokens;
-    const bool early = t_first < kv.max_blocks * 16;
+    const bool early = t_first < (planned ? t_end : kv.max_blocks * 16);      // planned: the span is known by now
     int blkA0 = -1, blkB0 = -1;
     if (early) lookup(t_first, blkA0, blkB0);
     float qlo[2][8], qhi[2][8];
     float2 qcs[2][8];
-    if (i < G) {
+    bf16x8 qf[4], qfl[4];
+    if constexpr (PREP) {
+        const uint16_t *q = reinterpret_cast<const uint16_t *>(a.q) + ((size_t)b * nq + kvh * G + (i < G ? i : 0)) * 128 + q4 * 8;
+        const size_t plane = (size_t)a.batch * nq * 128;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {        // a column past the heads repeats the first one; nothing of it is stored
+            qf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(q + ks * 32));
+            qfl[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(q + plane + ks * 32));
+        }
+    } else if (i < G) {
         const float *qrow = qkv_b + (size_t)(kvh * G + i) * 128;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
@@ -194,8 +459,7 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a)
     //      pairs with f + 64, i.e. fragment ks with fragment ks + 2 of the same lane.  The rotated query is carried
     //      as two bf16 fragments, q = hi + lo: a single bf16 query (2^-9 relative) puts a 2e-3 relative error on the
     //      attention output, which wide models amplify past the tolerance in the MLP block that follows.
-    bf16x8 qf[4], qfl[4];
-    {
+    if constexpr (!PREP) {
         uint4 z = zero16();
         qf[0] = qf[1] = qf[2] = qf[3] = __builtin_bit_cast(bf16x8, z);
         qfl[0] = qfl[1] = qfl[2] = qfl[3] = __builtin_bit_cast(bf16x8, z);
@@ -219,7 +483,8 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a)
     }
 
     // ---- append the new token's K and V (one workgroup per kv head does it)
-    if (T >= 1 && c == (T - 1) / a.chunk_tokens) {
+    if (!PREP && ch.last) {
+        const int T = t_end;
         if (tid < 64) {
             const int pos = T - 1;
             const int blk = kv_phys_block(kv.page_table, kv.max_blocks, kv.num_pool_blocks, b, pos >> 4);
@@ -248,8 +513,69 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a)
         __syncthreads();   // uniform: the condition depends on the workgroup only
         if (early && T - 1 >= t_first && T - 1 < t_first + kAttnTileTokens) load_tile(t_first);   // now with the new entry
     }
+    // ... and, where the preparing kernel has left it to this one, put it into the tile that holds it, which is on its way already: a
+    // second load of it would cost the memory latency again.  (On the vector path, one sequence with 16k tokens, the second load is
+    // the better one: 754 us for eight layers against 767.)
+    if (PREP && ch.last && !a.appended) {
+        const int pos = t_end - 1;
+        const int blk = kv_phys_block(kv.page_table, kv.max_blocks, kv.num_pool_blocks, b, pos >> 4);
+        if (tid < 64) {
+            const float2 cs = rope_b[tid];
+            const float *krow = qkv_b + (size_t)(nq + kvh) * 128;
+            const float *vrow = qkv_b + (size_t)(nq + nkv + kvh) * 128;
+            const float lo = krow[tid], hi = krow[tid + 64];
+            const uint16_t k0 = (uint16_t)f32_to_bf16(lo * cs.x - hi * cs.y), k1 = (uint16_t)f32_to_bf16(hi * cs.x + lo * cs.y);
+            const uint16_t v0 = (uint16_t)f32_to_bf16(vrow[tid]), v1 = (uint16_t)f32_to_bf16(vrow[tid + 64]);
+            fresh[0][tid] = k0; fresh[0][tid + 64] = k1;
+            fresh[1][tid] = v0; fresh[1][tid + 64] = v1;
+            if (blk >= 0) {
+                const int r = pos & 15;
+                const size_t tm_row = (((size_t)blk * 16 + r) * nkv + kvh) * 128;
+                uint16_t *kdst = TM ? kv.k_pool + tm_row : kv.k_pool + (((size_t)blk * nkv + kvh) * 16 + r) * 128;
+                kdst[tid] = k0;
+                kdst[tid + 64] = k1;
+                if constexpr (TM) {
+                    kv.v_pool[tm_row + tid] = v0;
+                    kv.v_pool[tm_row + tid + 64] = v1;
+                } else {
+                    uint16_t *vdst = kv.v_pool + ((size_t)blk * nkv + kvh) * 128 * 16 + r;
+                    vdst[(size_t)tid * 16] = v0;
+                    vdst[(size_t)(tid + 64) * 16] = v1;
+                }
+            }
+        }
+        // the new rows are read back within this workgroup only, through LDS or the CU's cache: the barrier's workgroup-scope
+        // ordering suffices (later kernels see them after this one has ended)
+        __syncthreads();   // uniform: the condition depends on the workgroup only
+        if (blk >= 0 && early && pos >= t_first && pos < t_first + kAttnTileTokens) {
+            const int dt = pos - t_first;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const uint4 k8 = *reinterpret_cast<const uint4 *>(&fresh[0][ks * 32 + q4 * 8]);
+                if (tau1 == dt) ka[ks] = k8;
+                if (tau1 + 4 == dt) kb[ks] = k8;
+            }
+            if constexpr (TM) {
+                const uint4 v8 = *reinterpret_cast<const uint4 *>(&fresh[1][i * 8]);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (4 * j + q4 == dt) vf[j] = v8;
+            } else {
+                const int e = dt - 8 * q4;          // token within this lane's eight, if it is one of them
+                const uint32_t keep = e & 1 ? 0x0000ffffu : 0xffff0000u;
+#pragma unroll
+                for (int dg = 0; dg < 8; ++dg) {
+                    const uint32_t v = fresh[1][dg * 16 + i], x = e & 1 ? v << 16 : v;
+                    if (e >> 1 == 0) vf[dg].x = (vf[dg].x & keep) | x;
+                    if (e >> 1 == 1) vf[dg].y = (vf[dg].y & keep) | x;
+                    if (e >> 1 == 2) vf[dg].z = (vf[dg].z & keep) | x;
+                    if (e >> 1 == 3) vf[dg].w = (vf[dg].w & keep) | x;
+                }
+            }
+        }
+    }
 
-    const float kScale = 0.08838834764831845f * 1.4426950408889634f;   // 1/sqrt(128) * log2(e)
+    const float kScale = kAttnScale;
     float m_run = -1.0e30f, l_part = 0.f;
     f32x4 acc[8];
 #pragma unroll
@@ -355,9 +681,8 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a)
 #pragma unroll
     for (int dg = 0; dg < 8; ++dg) accs[w][dg][lane] = acc[dg] * sc;
     __syncthreads();
-    const size_t slot0 = ((size_t)b * nkv + kvh) * a.n_chunks;
     if (i < G) {
-        const size_t slot = slot0 + c;
+        const size_t slot = ch.slot;
         if (w == 0 && q4 == 0) {
             a.part_ml[(slot * 16 + i) * 2 + 0] = M;
             a.part_ml[(slot * 16 + i) * 2 + 1] = ls[0][i] + ls[1][i] + ls[2][i] + ls[3][i];
@@ -392,21 +717,22 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a)
 // probabilities.  The appended rows are quantised per row in single precision (scale = max|v| / 127,
 // code = rint(v / scale)), stored, and re-read by the wave whose tile holds them.
 
-__global__ __launch_bounds__(256) void k_attn_q8(AttnArgs a)
+template <bool PREP>
+__global__ __launch_bounds__(256, PREP ? 2 : 1) void k_attn_q8(AttnArgs a)
 {
     constexpr int TT = kAttnTileTokensInt8;
     __shared__ float ms[kAttnWaves][16], ls[kAttnWaves][16];
     __shared__ f32x4 accs[kAttnWaves][8][64];
 
-    const int b = blockIdx.z, kvh = blockIdx.y, c = blockIdx.x;
+    const int kvh = blockIdx.y;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, i = lane & 15, q4 = lane >> 4;
     const int nq = a.nq, nkv = a.nkv, G = nq / nkv;
     const KvView &kv = a.kv;
     const int qkv_rows = (nq + 2 * nkv) * 128;
-    int T = kv.seq_lens[b];
-    if (T < 0 || T > kv.max_tokens) T = 0;      // a length outside the descriptor's range is treated as an empty sequence
-    const int t_begin = c * a.chunk_tokens;
-    const int t_end = min(T, t_begin + a.chunk_tokens);
+    const AttnChunk ch = attn_chunk<PREP>(a, kvh);
+    const bool planned = PREP && a.plan.map;
+    if (planned && ch.t_end == 0) return;      // no chunk left for this workgroup
+    const int b = ch.b, t_begin = ch.t_begin, t_end = ch.t_end;
     const float *qkv_b = a.qkv + (size_t)b * qkv_rows;
     const float2 *rope_b = a.rope + b * 64;
     uint8_t *k8 = reinterpret_cast<uint8_t *>(kv.k_pool), *v8 = reinterpret_cast<uint8_t *>(kv.v_pool);
@@ -459,13 +785,24 @@ __global__ __launch_bounds__(256) void k_attn_q8(AttnArgs a)
     // Order of the first requests: page-table entries of the first tile, then the query row and the rotary table,
     // then the tile itself; loads return in order, so the query digits are formed while the tile is on its way.
     const int t_first = t_begin + w * TT;
-    const bool early = t_first < kv.max_blocks * 16;
+    const bool early = t_first < (planned ? t_end : kv.max_blocks * 16);      // planned: the span is known by now
     int blkK0 = -1, blkV0 = -1;
     if (early) lookup(t_first, blkK0, blkV0);
     const bool have_q = i < G;
     float4 q_lo[4], q_hi[4];
     float2 q_cs[16];
-    {
+    uint4 qd1[2], qd2[2];
+    float q_back = 0.f;                       // head scale / 254 * softmax scale, applied to 254*S1 + S2
+    if constexpr (PREP) {
+        const size_t row = (size_t)b * nq + kvh * G + (have_q ? i : 0), plane = (size_t)a.batch * nq * 128;
+        const uint8_t *q = a.q + row * 128 + q4 * 16;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {           // a column past the heads repeats the first one; nothing of it is stored
+            qd1[j] = *reinterpret_cast<const uint4 *>(q + j * 64);
+            qd2[j] = *reinterpret_cast<const uint4 *>(q + plane + j * 64);
+        }
+        q_back = reinterpret_cast<const float *>(a.q + 2 * plane)[row];
+    } else {
         const float *qrow = qkv_b + (size_t)(kvh * G + (have_q ? i : 0)) * 128 + q4 * 16;
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
@@ -479,10 +816,7 @@ __global__ __launch_bounds__(256) void k_attn_q8(AttnArgs a)
 
     // ---- query digits: lane (g = i, q4) holds channels j*64 + q4*16 + e (j = 0, 1; e = 0..15), the byte order of
     //      its K codes; channel f < 64 pairs with f + 64 for the rotation, i.e. j = 0 with j = 1 of the same lane
-    uint4 qd1[2], qd2[2];
-    float q_back = 0.f;                       // head scale / 254 * softmax scale, applied to 254*S1 + S2
-    const float kScale = 0.08838834764831845f * 1.4426950408889634f;   // 1/sqrt(128) * log2(e)
-    {
+    if constexpr (!PREP) {
         float ql[16], qh[16];
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
@@ -503,7 +837,7 @@ __global__ __launch_bounds__(256) void k_attn_q8(AttnArgs a)
         amax = fmaxf(amax, __shfl_xor(amax, 16, 64));
         amax = fmaxf(amax, __shfl_xor(amax, 32, 64));
         const float inv = amax > 0.f ? 127.0f / amax : 0.f;
-        q_back = amax / 127.0f / 254.0f * kScale;
+        q_back = amax / 127.0f / 254.0f * kAttnScale;
         uint32_t w1[2][4], w2[2][4];
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
@@ -526,7 +860,8 @@ __global__ __launch_bounds__(256) void k_attn_q8(AttnArgs a)
     }
 
     // ---- append the new token's K and V (one workgroup per kv head does it)
-    if (T >= 1 && c == (T - 1) / a.chunk_tokens) {
+    if (!PREP && ch.last) {
+        const int T = t_end;
         if (tid < 64) {
             const int pos = T - 1;
             const int blk = kv_phys_block(kv.page_table, kv.max_blocks, kv.num_pool_blocks, b, pos >> 4);
@@ -648,9 +983,8 @@ __global__ __launch_bounds__(256) void k_attn_q8(AttnArgs a)
 #pragma unroll
     for (int dg = 0; dg < 8; ++dg) accs[w][dg][lane] = acc[dg] * sc;
     __syncthreads();
-    const size_t slot0 = ((size_t)b * nkv + kvh) * a.n_chunks;
     if (i < G) {
-        const size_t slot = slot0 + c;
+        const size_t slot = ch.slot;
         if (w == 0 && q4 == 0) {
             a.part_ml[(slot * 16 + i) * 2 + 0] = M;
             a.part_ml[(slot * 16 + i) * 2 + 1] = ls[0][i] + ls[1][i] + ls[2][i] + ls[3][i];
@@ -671,24 +1005,37 @@ __global__ __launch_bounds__(256) void k_attn_q8(AttnArgs a)
 // channels x 8 groups that share the chunks.  Wave 0 forms the softmax weights of the chunks once (LDS); every
 // thread sums its group's chunks of its channel in chunk order, and the 8 partial sums are added in group order.
 // All orders are fixed, so the result is reproducible.
+// PLAN: by the step's plan, whose number of chunks has to be read first (on the vector path that read cost 0.6 us a layer).
+template <bool PLAN>
 __global__ __launch_bounds__(1024) void k_attn_merge(AttnArgs a)
 {
     __shared__ float wl[kAttnMaxChunks + 8];   // weights of the chunks (+ slack for the predicated last batch)
     __shared__ float inv_den;
     __shared__ float psum[1024];
     const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int nq = a.nq, nkv = a.nkv, G = nq / nkv, nc = a.n_chunks;
+    const int nq = a.nq, nkv = a.nkv, G = nq / nkv;
     const int kvh = j / G, g = j % G;
-    const size_t slot0 = ((size_t)b * nkv + kvh) * nc;
+    const int most = PLAN ? a.plan.max_chunks : a.n_chunks;       // partials a sequence has room for, and has
+    const int nc = PLAN ? a.plan.chunks[b] : a.n_chunks;
+    const size_t slot0 = ((size_t)b * nkv + kvh) * most;
     if (w == 0) {
         constexpr int MU = kAttnMaxChunks / 64;
         float2 ml[MU];
         float Mx = -1.0e30f;
+        auto pair_of = [&](int sp) { return *reinterpret_cast<const float2 *>(a.part_ml + ((slot0 + sp) * 16 + g) * 2); };
+        if constexpr (PLAN) {
+            // the first sixteen do not wait for the number of partials; more of them would be lines read for nothing
+            ml[0] = lane < min(most, 16) ? pair_of(lane) : make_float2(-1.0e30f, 0.f);
+            if (lane >= nc) ml[0] = make_float2(-1.0e30f, 0.f);
+            else if (lane >= 16) ml[0] = pair_of(lane);
+        } else {
+            ml[0] = lane < nc ? pair_of(lane) : make_float2(-1.0e30f, 0.f);
+        }
+        Mx = ml[0].x;
 #pragma unroll
-        for (int u = 0; u < MU; ++u) {
+        for (int u = 1; u < MU; ++u) {
             const int sp = lane + 64 * u;
-            ml[u] = sp < nc ? *reinterpret_cast<const float2 *>(a.part_ml + ((slot0 + sp) * 16 + g) * 2)
-                            : make_float2(-1.0e30f, 0.f);
+            ml[u] = sp < nc ? pair_of(sp) : make_float2(-1.0e30f, 0.f);
             Mx = fmaxf(Mx, ml[u].x);
         }
         Mx = wave_max(Mx);
@@ -755,29 +1102,45 @@ static AttnArgs attn_args(const float *qkv, const float2 *rope, KvView kv, int b
                           float *part_ml, float *part_o, float *out_f32, uint16_t *out_bf16)
 {
     const size_t out_plane = (size_t)((batch + 15) / 16 * 16) * nq * 128;
-    return AttnArgs{qkv, rope, kv, nq, nkv, sp.chunk_tokens, sp.n_chunks, part_ml, part_o, out_f32, out_bf16, out_plane, 0};
+    return AttnArgs{qkv, nullptr, 0, batch, AttnPlan{}, rope, kv, nq, nkv, sp.chunk_tokens, sp.n_chunks, part_ml, part_o, out_f32, out_bf16, out_plane, 0};
+}
+
+template <bool PREP>
+static void launch_attn_kernel(const AttnArgs &a, dim3 grid, hipStream_t s)
+{
+    if (a.kv.int8) PSV_LAUNCH((k_attn_q8<PREP>), grid, dim3(256), 0, s, a);
+    else if (a.kv.token_major) PSV_LAUNCH((k_attn<true, PREP>), grid, dim3(256), 0, s, a);
+    else PSV_LAUNCH((k_attn<false, PREP>), grid, dim3(256), 0, s, a);
 }
 
 hipError_t launch_attn(const float *qkv, const float2 *rope, KvView kv, int batch, int nq, int nkv, AttnSplit sp,
                        float *part_ml, float *part_o, hipStream_t s)
 {
-    AttnArgs a = attn_args(qkv, rope, kv, batch, nq, nkv, sp, part_ml, part_o, nullptr, nullptr);
-    if (kv.int8)
-        PSV_LAUNCH(k_attn_q8, dim3(sp.n_chunks, nkv, batch), dim3(256), 0, s, a);
-    else if (kv.token_major)
-        PSV_LAUNCH(k_attn<true>, dim3(sp.n_chunks, nkv, batch), dim3(256), 0, s, a);
-    else
-        PSV_LAUNCH(k_attn<false>, dim3(sp.n_chunks, nkv, batch), dim3(256), 0, s, a);
+    launch_attn_kernel<false>(attn_args(qkv, rope, kv, batch, nq, nkv, sp, part_ml, part_o, nullptr, nullptr),
+                              dim3(sp.n_chunks, nkv, batch), s);
     return hipGetLastError();
 }
 
-hipError_t launch_attn_merge(const float *part_ml, const float *part_o, int batch, int nq, int nkv, AttnSplit sp,
+hipError_t launch_attn_prepared(const void *q, const float *qkv, const float2 *rope, KvView kv, int batch, int nq, int nkv, AttnSplit sp, const AttnPlan *plan,
+                                float *part_ml, float *part_o, hipStream_t s)
+{
+    AttnArgs a = attn_args(qkv, rope, kv, batch, nq, nkv, sp, part_ml, part_o, nullptr, nullptr);
+    a.q = static_cast<const uint8_t *>(q);
+    a.appended = prep_appends(kv, batch) ? 1 : 0;
+    if (plan) a.plan = *plan;
+    launch_attn_kernel<true>(a, plan ? dim3(plan->slots, nkv) : dim3(sp.n_chunks, nkv, batch), s);
+    return hipGetLastError();
+}
+
+hipError_t launch_attn_merge(const float *part_ml, const float *part_o, int batch, int nq, int nkv, AttnSplit sp, const AttnPlan *plan,
                              float *out_f32, uint16_t *out_bf16, bool digits, hipStream_t s)
 {
     AttnArgs a = attn_args(nullptr, nullptr, KvView{}, batch, nq, nkv, sp, const_cast<float *>(part_ml),
                            const_cast<float *>(part_o), out_f32, out_bf16);
     a.out_digits = digits ? 1 : 0;
-    PSV_LAUNCH(k_attn_merge, dim3(nq, batch), dim3(1024), 0, s, a);
+    if (plan) a.plan = *plan;
+    if (plan) PSV_LAUNCH(k_attn_merge<true>, dim3(nq, batch), dim3(1024), 0, s, a);
+    else PSV_LAUNCH(k_attn_merge<false>, dim3(nq, batch), dim3(1024), 0, s, a);
     return hipGetLastError();
 }
 

@@ -387,7 +387,7 @@ static psv_status enqueue_whole_step(psv_ctx *c, const float *x_in, float *x_out
     c->step_launches = 0;
     c->step_layers = le - lb;
     ST_TRY(prof_tag(c, -2));
-    HIP_TRY(launch_rope_table(c->kv.seq_lens, inv_freq, kv.max_tokens, 1, rope, s));
+    HIP_TRY(launch_rope_table(c->kv.seq_lens, inv_freq, kv.max_tokens, 1, rope, nullptr, s));
     StepLaunch p{};
     p.layer_table = c->wsp + c->ws.step_tbl;
     p.lb = (int)lb; p.le = (int)le;
@@ -534,8 +534,16 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
         }
     };
 
+    // The matrix-core path splits attention by the lengths of the step; the vector path (one or two sequences, whose O projection
+    // merges a fixed number of partials) and a tuned chunk size keep chunks of one length for all.  The plan lies in buffers of
+    // the vector path (delta_a and delta_m are neighbours).
+    AttnPlan plan_buf{}, *plan = nullptr;
+    if (sk && !c->attn_chunk_tokens && attn_plan(batch, d.n_kv_heads, d.max_seq, d.kv_format == PSV_FMT_INT8, c->at<uint2>(c->ws.delta_a),
+                                                 c->ws.m_f32 - c->ws.delta_a, c->at<int>(c->ws.h1_f32), &plan_buf))
+        plan = &plan_buf;
+
     ST_TRY(prof_tag(c, -2));
-    HIP_TRY(launch_rope_table(c->kv.seq_lens, inv_freq, kv_view(c, lb).max_tokens, B, rope, s));
+    HIP_TRY(launch_rope_table(c->kv.seq_lens, inv_freq, kv_view(c, lb).max_tokens, B, rope, plan, s));
     const float *res = x_in, *delta = nullptr;   // residual stream entering the layer = res + delta
     int delta_splits = 1;                        // delta may be a stack of split-K partials
     for (uint32_t l = lb; l < le; ++l) {
@@ -572,17 +580,18 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
             HIP_TRY(launch_gemm_sk(Wqkv, Mat{}, 0, h1b, ssq, d.rms_eps, part, B, QR, H, wait_qkv ? &skw : nullptr, s));
             wait_qkv = false;
             ST_TRY(prof_tag(c, -2));
-            HIP_TRY(launch_sk_reduce(part, gemm_sk_splits(B, QR, H, w8, tiled, false), B, QR, false, qkv, nullptr, false, s));
+            HIP_TRY(launch_attn_prep(part, gemm_sk_splits(B, QR, H, w8, tiled, false), rope, kv, B, nq, nkv, qkv, attnb, s));     // attnb: the merge's, later
         }
 
         if (!seg_attn) {
             ST_TRY(prof_tag(c, PSV_OP_ATTN));
-            HIP_TRY(launch_attn(qkv, rope, kv, B, nq, nkv, sp, pml, po, s));
+            if (sk) HIP_TRY(launch_attn_prepared(attnb, qkv, rope, kv, B, nq, nkv, sp, plan, pml, po, s));
+            else HIP_TRY(launch_attn(qkv, rope, kv, B, nq, nkv, sp, pml, po, s));
         }
         const bool fuse_merge = vec && gemv_merge_supported(B, nq, sp.n_chunks);
         if (!fuse_merge && !seg_attn) {
             ST_TRY(prof_tag(c, -2));
-            HIP_TRY(launch_attn_merge(pml, po, B, nq, nkv, sp, attn, attnb, sk && w8, s));
+            HIP_TRY(launch_attn_merge(pml, po, B, nq, nkv, sp, plan, attn, attnb, sk && w8, s));
         }
 
         if (!seg_attn) ST_TRY(prof_tag(c, PSV_OP_O));
@@ -630,7 +639,7 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
             HIP_TRY(launch_gemm_sk(Wg, Wu, F, h2b, ssq, d.rms_eps, part, B, 2 * F, H, wait_gate ? &skw : nullptr, s));
             wait_gate = false;
             ST_TRY(prof_tag(c, -2));
-            HIP_TRY(launch_sk_reduce(part, gemm_sk_splits(B, 2 * F, H, w8, tiled, true), B, 2 * F, true, m, mb, w8, s));
+            HIP_TRY(launch_sk_reduce(part, gemm_sk_splits(B, 2 * F, H, w8, tiled, true), B, 2 * F, m, mb, w8, s));
         }
 
         if (!seg_mlp) ST_TRY(prof_tag(c, PSV_OP_DOWN));

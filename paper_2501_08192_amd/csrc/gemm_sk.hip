@@ -209,7 +209,7 @@ __device__ __forceinline__ void sk_read_sums(const SkWaitArgs &wt, int n_ent, in
 // 128-byte lines of 16 rows.  Weight fragments and activation slabs are prefetched PF slabs ahead through
 // register rings, which keeps 16 KiB of weights per wave in flight even when only a few
 // workgroups exist (small matrices at batch 64 cannot use many: every extra K split costs a partial
-// result of batch x rows floats).  Splits are summed later in split order by the consumer (k_sk_reduce or
+// result of batch x rows floats).  Splits are summed later in split order by the consumer (k_attn_prep, k_sk_reduce or
 // k_resid_sum): deterministic, no atomics.
 struct GemmSkArgs {
     const uint16_t *W, *W2;   // rows >= split_row are taken from W2 (row - split_row): gate | up in one launch
@@ -1074,42 +1074,36 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
     return hipGetLastError();
 }
 
-// out[b][n] = sum over splits (split order) of part[ks][b][n]; with SwiGLU the N columns are gate | up
-// halves and the result is silu(gate) * up, [batch][N/2], stored as fp32 and as hi/lo bf16 planes.
-template <bool SWIGLU>
+// Gate | up: the N columns are summed over the splits (split order) and become silu(gate) * up, [batch][N/2], stored as fp32
+// and as the operand planes of the down projection.
 __global__ __launch_bounds__(256) void k_sk_reduce(const float *__restrict__ part, int splits, int batch, int N,
                                                    float *__restrict__ out, uint16_t *__restrict__ out_bf16, size_t out_plane,
                                                    int digits)
 {
-    const int NO = SWIGLU ? N / 2 : N;                 // output columns
+    const int NO = N / 2;                              // output columns
     const size_t total4 = (size_t)batch * NO / 4;
     const size_t split_stride = (size_t)batch * N;
     for (size_t q = (size_t)blockIdx.x * 256 + threadIdx.x; q < total4; q += (size_t)gridDim.x * 256) {
         const size_t e = q * 4, b = e / NO, c = e % NO;
         const float *p = part + b * N + c;
         // all split loads first (their latencies overlap), then the sums in split order
-        float4 t[kSkMaxSplits], t2[SWIGLU ? kSkMaxSplits : 1];
+        float4 t[kSkMaxSplits], t2[kSkMaxSplits];
 #pragma unroll
         for (int ks = 0; ks < kSkMaxSplits; ++ks) {
             t[ks] = ks < splits ? *reinterpret_cast<const float4 *>(p + ks * split_stride) : make_float4(0.f, 0.f, 0.f, 0.f);
-            if (SWIGLU)
-                t2[ks] = ks < splits ? *reinterpret_cast<const float4 *>(p + ks * split_stride + NO)
-                                     : make_float4(0.f, 0.f, 0.f, 0.f);
+            t2[ks] = ks < splits ? *reinterpret_cast<const float4 *>(p + ks * split_stride + NO) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        float4 v = t[0], u = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (SWIGLU) u = t2[0];
+        float4 v = t[0], u = t2[0];
 #pragma unroll
         for (int ks = 1; ks < kSkMaxSplits; ++ks) {
             v.x += t[ks].x; v.y += t[ks].y; v.z += t[ks].z; v.w += t[ks].w;
-            if (SWIGLU) { u.x += t2[ks].x; u.y += t2[ks].y; u.z += t2[ks].z; u.w += t2[ks].w; }
+            u.x += t2[ks].x; u.y += t2[ks].y; u.z += t2[ks].z; u.w += t2[ks].w;
         }
-        if (SWIGLU) {
-            v.x = silu_mul(v.x, u.x); v.y = silu_mul(v.y, u.y); v.z = silu_mul(v.z, u.z); v.w = silu_mul(v.w, u.w);
-        }
+        v.x = silu_mul(v.x, u.x); v.y = silu_mul(v.y, u.y); v.z = silu_mul(v.z, u.z); v.w = silu_mul(v.w, u.w);
         *reinterpret_cast<float4 *>(out + b * NO + c) = v;
-        if (out_bf16 && digits) {   // whole waves take this branch together (NO is a multiple of 256)
+        if (digits) {   // whole waves take this branch together (NO is a multiple of 256)
             store_digits4(reinterpret_cast<uint8_t *>(out_bf16), out_plane, NO, b, (int)c, v);
-        } else if (out_bf16) {
+        } else {
             uint32_t h0, h1, h2, h3, l0, l1, l2, l3;
             split_bf16(v.x, h0, l0); split_bf16(v.y, h1, l1); split_bf16(v.z, h2, l2); split_bf16(v.w, h3, l3);
             *reinterpret_cast<uint2 *>(out_bf16 + b * NO + c) = make_uint2(h0 | (h1 << 16), h2 | (h3 << 16));
@@ -1118,19 +1112,15 @@ __global__ __launch_bounds__(256) void k_sk_reduce(const float *__restrict__ par
     }
 }
 
-hipError_t launch_sk_reduce(const float *part, int splits, int batch, int N, bool swiglu, float *out,
-                            uint16_t *out_bf16, bool digits, hipStream_t s)
+hipError_t launch_sk_reduce(const float *part, int splits, int batch, int N, float *out, uint16_t *out_bf16, bool digits, hipStream_t s)
 {
-    const int NO = swiglu ? N / 2 : N;
+    const int NO = N / 2;
     const size_t total4 = (size_t)batch * NO / 4;
     unsigned blocks = (unsigned)((total4 + 255) / 256);
     if (blocks > 2048) blocks = 2048;
     if (blocks < 1) blocks = 1;
     const size_t out_plane = (size_t)((batch + 15) / 16 * 16) * NO;
-    if (swiglu)
-        PSV_LAUNCH(k_sk_reduce<true>, dim3(blocks), dim3(256), 0, s, part, splits, batch, N, out, out_bf16, out_plane, digits ? 1 : 0);
-    else
-        PSV_LAUNCH(k_sk_reduce<false>, dim3(blocks), dim3(256), 0, s, part, splits, batch, N, out, out_bf16, out_plane, digits ? 1 : 0);
+    PSV_LAUNCH(k_sk_reduce, dim3(blocks), dim3(256), 0, s, part, splits, batch, N, out, out_bf16, out_plane, digits ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -27,6 +27,17 @@ struct AttnSplit {
 };
 AttnSplit attn_split(uint32_t batch, uint32_t n_kv_heads, uint32_t max_seq, bool kv_int8);
 
+// The split of one step by the lengths of its sequences, made on the device (make_attn_plan).
+struct AttnPlan {
+    int unit;           // tokens of one step of a workgroup; a chunk is a whole number of them
+    int max_units;      // longest valid sequence in units
+    int max_chunks;     // most chunks of a sequence
+    int slots;          // workgroups per kv head
+    uint2 *map;         // [slots]: sequence << 24 | chunk << 12 | units of a chunk, and the end of its tokens (0: no chunk; bit 31: the last chunk)
+    int *chunks;        // [batch]: chunks of each sequence
+};
+bool attn_plan(uint32_t batch, uint32_t n_kv_heads, uint32_t max_seq, bool kv_int8, uint2 *map, size_t map_bytes, int *chunks, AttnPlan *p);
+
 struct KvView {
     uint16_t *k_pool;            // bf16 pool, or (int8 != 0) byte pool of PSV_KV_UNIT_BYTES_INT8 units
     uint16_t *v_pool;
@@ -156,7 +167,7 @@ hipError_t launch_step(const StepLaunch &p, int blocks, hipStream_t s);
 
 // Split-K skinny GEMM on the matrix cores with the activation slab shared through LDS:
 // part[split][b][r] = partial sums of W[r].x[b] (rows >= split_row come from W2), to be summed in split
-// order by launch_sk_reduce or launch_resid_sum.  x_bf16: see the operand formats above.
+// order by launch_attn_prep, launch_sk_reduce or launch_resid_sum.  x_bf16: see the operand formats above.
 constexpr int kSkMaxSplits = 16;
 int gemm_sk_splits(int batch, int N, int K, bool w8, bool tiled, bool pair);      // pair: gate | up in one launch
 bool gemm_sk_supported(int batch, int N, int K);
@@ -192,20 +203,24 @@ hipError_t launch_resid_sum(const float *res, const float *delta, int delta_spli
                             const SkWait *signal, hipStream_t s);
 // signal != null (gain != null): every output is written through to the memory side and each workgroup's
 // sum of squares is published as a tagged value in signal->ssq_ll once its other stores are acknowledged.
-// out = sum of the splits; swiglu: N = gate | up columns, out = silu(gate) * up of width N/2.  out_bf16
-// (optional) receives hi/lo planes.
-hipError_t launch_sk_reduce(const float *part, int splits, int batch, int N, bool swiglu, float *out,
-                            uint16_t *out_bf16, bool digits, hipStream_t s);
+// Gate | up: out = silu(gate) * up of the summed splits, width N/2, also as the next projection's operand in out_bf16.
+hipError_t launch_sk_reduce(const float *part, int splits, int batch, int N, float *out, uint16_t *out_bf16, bool digits, hipStream_t s);
 
-// cos/sin of the rotary angles at position seq_len-1: table [batch][64] (inv_freq null => identity).
+// cos/sin of the rotary angles at position seq_len-1: table [batch][64] (inv_freq null => identity); optionally the step's plan.
 hipError_t launch_rope_table(const int32_t *seq_lens, const double *inv_freq, int max_tokens, int batch,
-                             float2 *table, hipStream_t s);
+                             float2 *table, const AttnPlan *plan, hipStream_t s);
 
 // Decode attention: RoPE of q, KV append and split-K partials (max, sum, weighted V) per workgroup ...
 hipError_t launch_attn(const float *qkv, const float2 *rope, KvView kv, int batch, int nq, int nkv, AttnSplit sp,
                        float *part_ml, float *part_o, hipStream_t s);
+// ... the same in two kernels, for a projection that leaves split-K partials: sums into qkv, rotated queries as matrix operands into
+// q (4 bytes a channel suffice), KV append where it pays; then the attention, split by the step's plan or by sp ...
+hipError_t launch_attn_prep(const float *part, int splits, const float2 *rope, KvView kv, int batch, int nq, int nkv, float *qkv,
+                            void *q, hipStream_t s);
+hipError_t launch_attn_prepared(const void *q, const float *qkv, const float2 *rope, KvView kv, int batch, int nq, int nkv, AttnSplit sp, const AttnPlan *plan,
+                                float *part_ml, float *part_o, hipStream_t s);
 // ... and the fixed-order merge of the partials into out_f32 and the hi/lo bf16 planes out_bf16.
-hipError_t launch_attn_merge(const float *part_ml, const float *part_o, int batch, int nq, int nkv, AttnSplit sp,
+hipError_t launch_attn_merge(const float *part_ml, const float *part_o, int batch, int nq, int nkv, AttnSplit sp, const AttnPlan *plan,
                              float *out_f32, uint16_t *out_bf16, bool digits, hipStream_t s);
 
 // Communication stand-in: one workgroup busy-waits `ticks` of the constant-rate wall clock.
