@@ -239,11 +239,17 @@ struct GemmSkArgs {
 // window's prefetch kernel as well: it walks the job first, before anything of its own sits in registers.
 __device__ __forceinline__ uint32_t xor4(uint4 v) { return v.x ^ v.y ^ v.z ^ v.w; }
 
-template <int NB, int HOLD>
+// APART: the products with the activations' lo plane are summed apart from those with the hi plane and added at the end, so that
+// the sum that carries the magnitude is rounded twice a slab instead of four times.  One matrix (QKV, O, down) takes it, whose
+// ranges are up to twice as long as a chip filled with two workgroups a CU would give it (gemm_sk_splits); gate | up keeps its
+// short ranges and the registers of its waiting form.  Distance of the QKV sums from 64 bits at 11 slabs a range: one sum 2.44e-7,
+// apart 1.73e-7 (eight slabs a range, one sum: 2.18e-7); a step takes as long either way.
+template <int NB, int HOLD, bool APART>
 __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj)
 {
     constexpr bool WAIT = HOLD > 0;
     static_assert(!WAIT || NB <= 2, "the waiting variant is built for one or two batch tiles");
+    static_assert(!WAIT || !APART, "gate | up has one order of sums, launched ahead or not");
     constexpr int PF = 4;   // slabs of weight fragments in flight per wave (8 measured slower: fewer straight-line rounds, more registers)
     // [buffer][(batch tile*2 + plane)*2 + k half][lane].  Eight neighbouring threads hold the eight 16-byte segments of one batch
     // row, whose fragment slots lie 256 bytes apart: all on the same banks.  Slot ^ segment spreads them over eight bank groups, and
@@ -314,6 +320,13 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
         for (int n = 0; n < NB; ++n) acc[mt][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 acc_lo[APART ? 2 : 1][APART ? NB : 1];
+    if constexpr (APART) {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int n = 0; n < NB; ++n) acc_lo[mt][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     __shared__ float inv_s[NB * 16];
 
     // WAIT: the first PF slabs of the range wait in the register ring as always, the next RH in registers of their own
@@ -441,8 +454,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
                 const bf16x8 a1 = __builtin_bit_cast(bf16x8, f.a1[mt]);
                 acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bh0, acc[mt][n], 0, 0, 0);
                 acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bh1, acc[mt][n], 0, 0, 0);
-                acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bl0, acc[mt][n], 0, 0, 0);
-                acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bl1, acc[mt][n], 0, 0, 0);
+                f32x4 &lo = APART ? acc_lo[APART ? mt : 0][APART ? n : 0] : acc[mt][n];
+                lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, bl0, lo, 0, 0, 0);
+                lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, bl1, lo, 0, 0, 0);
             }
         }
     };
@@ -535,6 +549,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
         __syncthreads();
         inv_rms();
         __syncthreads();
+    }
+    if constexpr (APART) {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int n = 0; n < NB; ++n) acc[mt][n] += acc_lo[mt][n];
     }
     // D fragment: lane holds rows 4g..4g+3 of batch column i
     float *part = a.part + (size_t)blockIdx.y * a.batch * a.N;
@@ -961,12 +981,12 @@ static const SkWaitRes &sk_wait_res()
             q.regs[kind][lv] = (at.numRegs + 7) / 8 * 8;
             q.lds[kind][lv] = (int)at.sharedSizeBytes;
         };
-        ask(0, 0, k_gemm_sk<1, 1>);
-        ask(0, 1, k_gemm_sk<1, 2>);
+        ask(0, 0, k_gemm_sk<1, 1, false>);
+        ask(0, 1, k_gemm_sk<1, 2, false>);
         ask(1, 0, k_gemm_sk_i8<1, 1>);
         ask(1, 1, k_gemm_sk_i8<1, 2>);
-        ask(2, 0, k_gemm_sk<2, 1>);
-        ask(2, 1, k_gemm_sk<2, 2>);
+        ask(2, 0, k_gemm_sk<2, 1, false>);
+        ask(2, 1, k_gemm_sk<2, 2, false>);
         hipFuncAttributes at{};
         q.ok = q.ok && hipFuncGetAttributes(&at, reinterpret_cast<const void *>(k_resid_sum<true>)) == hipSuccess;
         q.regs_signal = (at.numRegs + 7) / 8 * 8;
@@ -1058,17 +1078,21 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
         fill_wait(a.wt, a.slabs_per_block);
         const PrefetchJob pj = wait->job ? *wait->job : PrefetchJob{};
         const int lv = sk_hold_level(a.slabs_per_block, nb);
-        if (nb == 1 && lv == 2) PSV_LAUNCH((k_gemm_sk<1, 2>), grid, dim3(256), 0, s, a, pj);
-        else if (nb == 1) PSV_LAUNCH((k_gemm_sk<1, 1>), grid, dim3(256), 0, s, a, pj);
-        else if (lv == 2) PSV_LAUNCH((k_gemm_sk<2, 2>), grid, dim3(256), 0, s, a, pj);
-        else PSV_LAUNCH((k_gemm_sk<2, 1>), grid, dim3(256), 0, s, a, pj);
+        if (nb == 1 && lv == 2) PSV_LAUNCH((k_gemm_sk<1, 2, false>), grid, dim3(256), 0, s, a, pj);
+        else if (nb == 1) PSV_LAUNCH((k_gemm_sk<1, 1, false>), grid, dim3(256), 0, s, a, pj);
+        else if (lv == 2) PSV_LAUNCH((k_gemm_sk<2, 2, false>), grid, dim3(256), 0, s, a, pj);
+        else PSV_LAUNCH((k_gemm_sk<2, 1, false>), grid, dim3(256), 0, s, a, pj);
         return hipGetLastError();
     }
-    switch (nb) {
-    case 1: PSV_LAUNCH((k_gemm_sk<1, 0>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 2: PSV_LAUNCH((k_gemm_sk<2, 0>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 3: PSV_LAUNCH((k_gemm_sk<3, 0>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 4: PSV_LAUNCH((k_gemm_sk<4, 0>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    switch (W2.w ? nb : nb + 4) {        // one matrix: the planes' products summed apart
+    case 1: PSV_LAUNCH((k_gemm_sk<1, 0, false>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    case 2: PSV_LAUNCH((k_gemm_sk<2, 0, false>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    case 3: PSV_LAUNCH((k_gemm_sk<3, 0, false>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    case 4: PSV_LAUNCH((k_gemm_sk<4, 0, false>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    case 5: PSV_LAUNCH((k_gemm_sk<1, 0, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    case 6: PSV_LAUNCH((k_gemm_sk<2, 0, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    case 7: PSV_LAUNCH((k_gemm_sk<3, 0, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    case 8: PSV_LAUNCH((k_gemm_sk<4, 0, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
