@@ -47,7 +47,10 @@
  *    even.  Activations stay in floating point.
  *  - seq_lens[b] is the attention span INCLUDING the token decoded by the step: the step
  *    writes slot seq_lens[b]-1 of every layer's cache and attends over [0, seq_lens[b]).
- *    It never changes seq_lens or the page table, so repeating a call is idempotent.
+ *    It never changes seq_lens or the page table, so repeating a call is idempotent: the same bits every time.
+ *  - From batch 3 on (batch 2 with hidden > 4096, tiled weights at any batch) the attention is divided over the chip by the lengths of the whole batch, so
+ *    the last bits of a sequence's result depend on the lengths of the others; psv_set_attention_chunk (preserve_aux.h) fixes the
+ *    division where a sequence's bits have to depend on the sequence alone.
  *  - Every entry point returns a psv_status (0 = ok, negative = error); nothing throws, aborts
  *    or prints.  Argument checks are done on the host before anything is launched.
  *    Asynchronous HIP errors surface at psv_sync.

@@ -45,6 +45,18 @@ psv_status psv_set_fused_kernels(psv_ctx *ctx, uint32_t on);
 
 /* ---- streams and tuning -------------------------------------------------------------------- */
 
+/* How many tokens of a sequence one attention workgroup covers: chunk_tokens for every sequence of every later step of this
+ * context, or 0 (the state of a new context) for the library's own split.  On the matrix-core path (batch 3 and more, batch
+ * 2 with hidden > 4096, tiled weights at any batch) the library divides the lengths of each step: the smallest chunk size with which the chunks of all
+ * sequences fit one round of workgroups.  With it the summation order of a sequence, and so its last bits, depends on the lengths
+ * of the other sequences in the batch; with a chunk size set here, and on the vector path in either case, it depends on the
+ * sequence alone (at one batch size).  chunk_tokens: a multiple of 128 (int8 cache: 256), at most max_seq rounded up to that, at
+ * least max_seq / 256; anything else is PSV_ERR_INVALID_ARG and changes nothing.  Settings agree to rounding, not bit for bit;
+ * within one setting every policy gives the same bits.  The fused kernels have a split of their own and take no notice. */
+psv_status psv_set_attention_chunk(psv_ctx *ctx, uint32_t chunk_tokens);
+/* *chunk_tokens = what is set (by this call or by psv_tune_attention), 0 for the library's own split. */
+psv_status psv_get_attention_chunk(psv_ctx *ctx, uint32_t *chunk_tokens);
+
 /* Chooses how many tokens of a sequence one attention workgroup covers (the split of the span over
  * workgroups).  The default comes from a heuristic on (max_batch, kv heads, max_seq); which split is fastest
  * depends on the shape in ways a heuristic captures only roughly (measured spread over the candidates: 10 %;

@@ -261,6 +261,24 @@ psv_status psv_check_overlap(psv_ctx *c, int32_t *concurrent)
     return psv_sync(c);
 }
 
+psv_status psv_set_attention_chunk(psv_ctx *c, uint32_t chunk_tokens)
+{
+    if (!c) return PSV_ERR_INVALID_ARG;
+    const uint32_t unit = (c->d.kv_format == PSV_FMT_INT8 ? kAttnTileTokensInt8 : kAttnTileTokens) * kAttnWaves;
+    const uint32_t units = (c->d.max_seq + unit - 1) / unit;      // of the longest sequence; more in a chunk would change nothing
+    if (chunk_tokens % unit || chunk_tokens / unit > units) return PSV_ERR_INVALID_ARG;
+    if (chunk_tokens && (c->d.max_seq + chunk_tokens - 1) / chunk_tokens > (uint32_t)kAttnMaxChunks) return PSV_ERR_INVALID_ARG;
+    c->attn_chunk_tokens = chunk_tokens;
+    return PSV_OK;
+}
+
+psv_status psv_get_attention_chunk(psv_ctx *c, uint32_t *chunk_tokens)
+{
+    if (!c || !chunk_tokens) return PSV_ERR_INVALID_ARG;
+    *chunk_tokens = c->attn_chunk_tokens;
+    return PSV_OK;
+}
+
 psv_status psv_tune_attention(psv_ctx *c, const float *x_in, float *x_out, uint32_t batch, uint32_t *chunk_tokens)
 {
     if (!c || !x_in || !x_out || batch == 0 || batch > c->d.max_batch) return PSV_ERR_INVALID_ARG;
