@@ -57,16 +57,16 @@ psv_status psv_set_attention_chunk(psv_ctx *ctx, uint32_t chunk_tokens);
 /* *chunk_tokens = what is set (by this call or by psv_tune_attention), 0 for the library's own split. */
 psv_status psv_get_attention_chunk(psv_ctx *ctx, uint32_t *chunk_tokens);
 
-/* Chooses how many tokens of a sequence one attention workgroup covers (the split of the span over
- * workgroups).  The default comes from a heuristic on (max_batch, kv heads, max_seq); which split is fastest
- * depends on the shape in ways a heuristic captures only roughly (measured spread over the candidates: 10 %;
- * the default lands within 1-2 % of the best on the shapes it was centred on), so this call times
- * psv_decode_step(ctx, x_in, x_out, batch, 0, 1) -- layer 0 only, prefetching off, no windows -- for a list of
- * candidate splits and keeps the fastest for all later steps of this context.  It has the side effects of that
- * decode step (x_out, slot seq_lens[b]-1 of layer 0's cache) and needs weights of layer 0 and the KV-cache set.
- * The split changes the summation order of the attention partials, i.e. results before and after tuning agree
- * to rounding, not bit for bit; within one split they stay bit-identical for every policy.  *chunk_tokens
- * (optional) receives the choice.  Synchronises both streams. */
+/* Chooses between the library's own split and chunk sizes for all sequences (psv_set_attention_chunk) by timing
+ * psv_decode_step(ctx, x_in, x_out, batch, 0, 1) -- layer 0 only, prefetching off, no windows -- for each, at the lengths that
+ * seq_lens holds now, and keeps the fastest for all later steps of this context.  The library's own split is by the lengths of each
+ * step on the matrix-core path and a rule on (max_batch, kv heads, max_seq) on the vector path, within 1-2 % of the best on the
+ * shapes it was centred on.  A chunk size that wins here stays as it is when the lengths change: tune at lengths the context
+ * will see, or set 0 again.  (The list of the step's lengths, made once a step, is charged to every candidate alike.)
+ * The call has the side effects of that decode step (x_out, slot seq_lens[b]-1 of layer 0's cache) and needs weights of layer 0
+ * and the KV-cache set.  Results before and after agree to rounding, not bit for bit.  *chunk_tokens (optional) receives the
+ * tokens a workgroup covered under the choice at the timed lengths; psv_get_attention_chunk says whether a size was set.
+ * Synchronises both streams. */
 psv_status psv_tune_attention(psv_ctx *ctx, const float *x_in, float *x_out, uint32_t batch,
                               uint32_t *chunk_tokens);
 

@@ -294,36 +294,65 @@ psv_status psv_tune_attention(psv_ctx *c, const float *x_in, float *x_out, uint3
     c->window_us[0] = c->window_us[1] = 0.f;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) st = PSV_ERR_HIP;
-    uint32_t best = 0;
-    float best_ms = 0.f;
+    uint32_t best = 0;                                 // 0: the library's own split
+    float best_ms = -1.f;
+    const uint32_t saved_chunk = c->attn_chunk_tokens;
+    bool planned = false;                              // ... is by the lengths of the step, not by def
     const AttnSplit def = attn_split(d.max_batch, d.n_kv_heads, d.max_seq, d.kv_format == PSV_FMT_INT8);
     static const uint32_t mult[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 11, 12, 14, 16, 20, 24, 28, 32, 40, 48, 64};
-    for (int k = -1; k < (int)(sizeof mult / sizeof mult[0]) && st == PSV_OK; ++k) {
-        const uint32_t chunk = k < 0 ? (uint32_t)def.chunk_tokens : mult[k] * unit;
+    constexpr int kMult = (int)(sizeof mult / sizeof mult[0]);
+    uint32_t cand[kMult + 2] = {0, (uint32_t)def.chunk_tokens};      // the library's own split, and chunks of def where that is another one
+    float cand_ms[kMult + 2];
+    int n_cand = 2;
+    for (uint32_t m : mult) {
+        const uint32_t chunk = m * unit;
         const uint64_t n_chunks = ((uint64_t)d.max_seq + chunk - 1) / chunk;
-        if (n_chunks > (uint64_t)kAttnMaxChunks || (k >= 0 && chunk == (uint32_t)def.chunk_tokens)) continue;
+        if (n_chunks > (uint64_t)kAttnMaxChunks || chunk == (uint32_t)def.chunk_tokens) continue;
         const uint64_t wgs = n_chunks * d.n_kv_heads * batch;
-        if (k >= 0 && (wgs > 8192 || (wgs < 128 && chunk > unit))) continue;   // far from filling the chip, or a long tail of rounds
-        c->attn_chunk_tokens = k < 0 ? 0 : chunk;      // 0: what a context runs that keeps the default
-        float ms = 0.f;
-        for (int rep = 0; rep < 2 + 8 && st == PSV_OK; ++rep) {
-            if (rep == 2 && hipEventRecord(e0, c->main) != hipSuccess) st = PSV_ERR_HIP;
-            if (st == PSV_OK) st = enqueue_step(c, x_in, x_out, batch, 0, 1);
-        }
-        if (st == PSV_OK && (hipEventRecord(e1, c->main) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-                             hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
-            st = PSV_ERR_HIP;
-        if (st == PSV_OK && (best == 0 || ms < best_ms)) { best = chunk; best_ms = ms; }
+        if (wgs > 8192 || (wgs < 128 && chunk > unit)) continue;      // far from filling the chip, or a long tail of rounds
+        cand[n_cand++] = chunk;
     }
+    // The steps of a candidate are enqueued behind a wait that outlasts their enqueueing, so that the device and not the host is timed;
+    // a candidate's time is its faster one of two passes, the first of which also wakes the device.  (Enqueued into an idle queue,
+    // the candidate that came first was measured at 57-90 us for a step that takes 44.)
+    const float wait_us = 600.f;
+    c->attn_tuning = true;
+    for (int pass = 0; pass < 2; ++pass)
+        for (int k = 0; k < n_cand && st == PSV_OK; ++k) {
+            if (k == 1 && !planned) continue;
+            c->attn_chunk_tokens = cand[k];
+            float ms = 0.f;
+            if (launch_spin(us_to_ticks(c->clock_khz, wait_us), spin_cap(wait_us), nullptr, nullptr, 0, c->main) != hipSuccess) st = PSV_ERR_HIP;
+            for (int rep = 0; rep < 2 + 8 && st == PSV_OK; ++rep) {
+                if (rep == 2 && hipEventRecord(e0, c->main) != hipSuccess) st = PSV_ERR_HIP;
+                if (st == PSV_OK) st = enqueue_step(c, x_in, x_out, batch, 0, 1);
+            }
+            if (st == PSV_OK && (hipEventRecord(e1, c->main) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+                                 hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
+                st = PSV_ERR_HIP;
+            if (k == 0) planned = c->last_step_planned;
+            if (pass == 0 || ms < cand_ms[k]) cand_ms[k] = ms;
+        }
+    for (int k = 0; k < n_cand && st == PSV_OK; ++k)
+        if (!(k == 1 && !planned) && (best_ms < 0.f || cand_ms[k] < best_ms)) { best = cand[k]; best_ms = cand_ms[k]; }
+    c->attn_tuning = false;
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     c->policy = saved_policy;
     c->window_us[0] = saved_win[0];
     c->window_us[1] = saved_win[1];
-    c->attn_chunk_tokens = (st == PSV_OK && best != (uint32_t)def.chunk_tokens) ? best : 0;
-    if (st == PSV_OK && chunk_tokens) *chunk_tokens = best;
+    c->attn_chunk_tokens = st == PSV_OK ? best : saved_chunk;
     const psv_status st2 = psv_sync(c);
-    return st != PSV_OK ? st : st2;
+    if (st != PSV_OK) return st;
+    if (st2 == PSV_OK && chunk_tokens) {
+        *chunk_tokens = best ? best : (uint32_t)def.chunk_tokens;
+        if (!best && planned) {      // the size that the list of the timed lengths has; every candidate's step has left it there
+            uint2 first{};
+            HIP_TRY(hipMemcpy(&first, c->at<uint2>(c->ws.delta_a), sizeof first, hipMemcpyDeviceToHost));
+            *chunk_tokens = (first.x & 0xfffu ? first.x & 0xfffu : 1u) * unit;
+        }
+    }
+    return st2;
 }
 
 psv_status psv_set_profile_op(psv_ctx *c, int32_t op)

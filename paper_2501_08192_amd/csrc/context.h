@@ -55,6 +55,8 @@ struct psv_ctx {
     uint32_t last_step_prelaunches = 0;          // consumers the last step launched into their windows
     unsigned window_seq = 0;                     // sequence number of the last communication window enqueued
     uint32_t attn_chunk_tokens = 0;               // 0 = default split; else tokens per attention workgroup (psv_set_attention_chunk, psv_tune_attention)
+    bool attn_tuning = false;                    // psv_tune_attention is timing candidates: every step makes the list of its lengths, used or not
+    bool last_step_planned = false;              // the last step's attention was split by the lengths of the step
     int overlap = -1;                            // psv_check_overlap's last answer (-1 = not run yet)
     bool check_err_word = false;                 // a kernel that may set the error word (a pre-launched consumer, a fused kernel) was launched: read it at sync
     int fused = 3;                               // psv_set_fused_kernels: 0 one kernel per operator, 1 one per block, 2 one per step, 3 by shape

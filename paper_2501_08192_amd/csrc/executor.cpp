@@ -485,7 +485,7 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
     }
     const int blocks = fused ? c->cus : 0;
     const uint32_t poll_iters = c->force_wait_timeout ? 0u : kSegPollIters;     // hand-overs inside the fused kernels
-    c->last_step_whole = false;
+    c->last_step_whole = c->last_step_planned = false;
     if (fused == 2 && vec && blocks >= 64 &&
         step_supported(B, H, F, nq, nkv, d.max_seq, d.kv_format == PSV_FMT_INT8 || d.kv_layout != PSV_KV_HEAD_MAJOR, w8, blocks))
         return enqueue_whole_step(c, x_in, x_out, lb, le, blocks);
@@ -537,13 +537,16 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
     // The matrix-core path splits attention by the lengths of the step; the vector path (one or two sequences, whose O projection
     // merges a fixed number of partials) and a tuned chunk size keep chunks of one length for all.  The plan lies in buffers of
     // the vector path (delta_a and delta_m are neighbours).
-    AttnPlan plan_buf{}, *plan = nullptr;
-    if (sk && !c->attn_chunk_tokens && attn_plan(batch, d.n_kv_heads, d.max_seq, d.kv_format == PSV_FMT_INT8, c->at<uint2>(c->ws.delta_a),
+    // (Timing candidates, every one of them pays for the list: a step makes it once, and a candidate's step is one layer.)
+    AttnPlan plan_buf{}, *made = nullptr;
+    if (sk && (!c->attn_chunk_tokens || c->attn_tuning) && attn_plan(batch, d.n_kv_heads, d.max_seq, d.kv_format == PSV_FMT_INT8, c->at<uint2>(c->ws.delta_a),
                                                  c->ws.m_f32 - c->ws.delta_a, c->at<int>(c->ws.h1_f32), &plan_buf))
-        plan = &plan_buf;
+        made = &plan_buf;
+    const AttnPlan *plan = c->attn_chunk_tokens ? nullptr : made;
+    c->last_step_planned = plan != nullptr;
 
     ST_TRY(prof_tag(c, -2));
-    HIP_TRY(launch_rope_table(c->kv.seq_lens, inv_freq, kv_view(c, lb).max_tokens, B, rope, plan, s));
+    HIP_TRY(launch_rope_table(c->kv.seq_lens, inv_freq, kv_view(c, lb).max_tokens, B, rope, made, s));
     const float *res = x_in, *delta = nullptr;   // residual stream entering the layer = res + delta
     int delta_splits = 1;                        // delta may be a stack of split-K partials
     for (uint32_t l = lb; l < le; ++l) {

@@ -91,7 +91,7 @@ class Session:
         psv.psv_set_comm_windows(self.ctx, float(us0), float(us1))
 
     def tune_attention(self):
-        """Times the candidate attention splits on layer 0 and keeps the fastest; returns tokens per workgroup."""
+        """Times the candidate attention splits on layer 0 and keeps the fastest; returns tokens per workgroup at the present lengths."""
         assert 0 in self.layers
         return psv.psv_tune_attention(self.ctx, self.x_in, self.x_out, self.w.batch)
 

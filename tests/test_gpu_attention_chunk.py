@@ -111,3 +111,18 @@ def test_chunk_sizes_that_cannot_be_are_refused_and_change_nothing():
     with Session(w.scaled(context=256 * 128 + 16, batch=1), seed=63) as s:                     # more than 256 chunks of 128
         assert psv.lib().psv_set_attention_chunk(s.ctx, 128) == psv.PSV_ERR_INVALID_ARG
         psv.psv_set_attention_chunk(s.ctx, 256)
+
+
+def test_tuning_keeps_the_split_by_length_where_it_is_the_faster_and_reports_its_chunk_size():
+    """One long sequence among short ones, far from filling the chip: the library's own split takes the smallest chunks for the few
+    tokens there are (measured 48 us a step), not those that divide the longest possible sequence (512 tokens, 53 us); the best
+    uniform size (384) takes 51."""
+    w = synth.Workload("tune", 1, 512, 4, 1, 128, 256, 24, 8192, False, (0.0, 0.0))
+    with Session(w, seed=64) as s:
+        s.seq_lens.copy_(torch.tensor([8192] + [64] * 23, dtype=torch.int32))
+        own = s.run().clone()
+        for rep in range(2):
+            assert s.tune_attention() == 128 and psv.psv_get_attention_chunk(s.ctx) == 0
+            assert torch.equal(s.run(), own)
+        psv.psv_set_attention_chunk(s.ctx, 512)
+        assert s.tune_attention() == 128 and psv.psv_get_attention_chunk(s.ctx) == 0       # whatever was set before
