@@ -6,7 +6,7 @@ predict the speedup map and to pick a prefetch budget.
 Per kernel:  t = t_fixed + hit_bytes / bw_cache + miss_bytes / bw_hbm, with one (t_fixed, bw_hbm, bw_cache) triple
 per kernel class: the vector-ALU projections of batch 1-2, the matrix-core projections of larger batches (on row-major
 and on tiled weights), the decode attention, and the small kernels the matrix-core path adds (residual sums, split-K
-reductions, attention merge).
+sums, attention merge).
 Per window:  t = max(window, t_fork + prefetch_bytes / bw_prefetch)   (the prefetch may outlast the window),
 and whatever part of a prefetch is still running after the window competes with its consumer for HBM.
 
@@ -42,7 +42,7 @@ class Machine:
     t_fixed_attn: float = 4.5
     bw_attn: float = 4.8e6
     bw_attn_cache: float = 5.5e6
-    # small kernels of the matrix-core path (2 residual sums, 2 split-K reductions, attention merge)
+    # small kernels of the matrix-core path (2 residual sums, QKV sums with the attention's operands, gate/up sums with SwiGLU, attention merge)
     t_small: float = 3.7
     n_small: int = 5
     # prefetch kernel
@@ -77,26 +77,30 @@ def path_of(batch, hidden, weight_layout="row"):
     return "vec" if batch == 1 or (batch == 2 and hidden <= 4096) else "mm"
 
 
-def sk_splits(batch, n_rows, k, weight_bytes=2.0, tiled=False):
-    """K splits of the split-K GEMM: the library's cost model for the gate/up pair and for int8 weights (0.6 us per slab step,
-    512 resident workgroups, weights and partials at 4 TB/s).  For one bf16 matrix (QKV, O, down) the library has since taken
-    to covering the chip once; the constants here were calibrated, and the recorded rows measured, with this rule throughout."""
+def sk_splits(batch, n_rows, k, weight_bytes=2.0, tiled=False, pair=True):
+    """K splits of the split-K GEMM: the library's own rule.  One matrix of bf16 weights (pair False: QKV, O, down): the fullest of
+    256 compute units walks ceil(workgroups / 256) ranges at 0.45 us a slab, partials at 5 TB/s.  The gate/up pair, and int8
+    weights: 0.6 us a slab, 512 resident workgroups, weights and partials at 4 TB/s."""
     n_slabs = k // 64
     row_groups = (n_rows + 127) // 128
     w_bytes, part_bytes = weight_bytes * n_rows * k, 8.0 * batch * n_rows
+    single = weight_bytes == 2.0 and not pair
     best, best_cost, best1, best1_cost = 1, 1e30, 0, 1e30
-    ks = 1
-    while ks <= 16 and ks * 2 <= n_slabs:
+    for ks in range(1, min(16, n_slabs // 2) + 1):
         spb = (n_slabs + ks - 1) // ks
-        if (n_slabs + spb - 1) // spb == ks:
+        if (n_slabs + spb - 1) // spb != ks:
+            continue
+        if single:
+            rounds = (row_groups * ks + 255) // 256
+            cost = rounds * spb * 0.45 + ks * part_bytes / 5.0e6
+        else:
             rounds = (row_groups * ks + 511) // 512
             cost = rounds * spb * 0.6 + (w_bytes + ks * part_bytes) / 4.0e6
-            if cost < best_cost - 1e-9:
-                best, best_cost = ks, cost
-            if rounds == 1 and cost < best1_cost - 1e-9:
-                best1, best1_cost = ks, cost
-        ks += 1
-    if tiled and best1 and best1_cost <= 1.02 * best_cost:      # tiled weights: within 2 %, one round of workgroups wins
+        if cost < best_cost - 1e-9:
+            best, best_cost = ks, cost
+        if rounds == 1 and cost < best1_cost - 1e-9:
+            best1, best1_cost = ks, cost
+    if not single and tiled and best1 and best1_cost <= 1.02 * best_cost:      # tiled weights: within 2 %, one round of workgroups wins
         best = best1
     return best
 
@@ -139,7 +143,7 @@ def op_bytes(hidden, n_q, n_kv, ffn, batch, context, head_dim=128, weight_format
            "gate": ffn * hidden * wb, "up": ffn * hidden * wb, "down": hidden * ffn * wb}
     mm = path_of(batch, hidden, weight_layout) != "vec"
     for name, rows, k in (("qkv", qkv_rows, hidden), ("o", hidden, n_q * head_dim), ("gate_up", 2 * ffn, hidden), ("down", hidden, ffn)):
-        out["p_" + name] = 8.0 * sk_splits(batch, rows, k, float(wb), weight_layout == "tiled") * batch * rows if mm else 0.0
+        out["p_" + name] = 8.0 * sk_splits(batch, rows, k, float(wb), weight_layout == "tiled", name == "gate_up") * batch * rows if mm else 0.0
     return out
 
 

@@ -1,5 +1,8 @@
 """The analytic latency model (paper Section 5, re-parameterised): consistency with the library's planner and
 the qualitative behaviour the paper and the measurements show.  CPU only."""
+import ctypes as C
+import itertools
+
 import pytest
 
 from paper_2501_08192_amd import binding as psv
@@ -39,6 +42,21 @@ def test_prefetch_off_is_the_plain_sum():
     assert model.path_of(1, 8192) == "vec" and model.path_of(2, 4096) == "vec" and model.path_of(2, 8192) == "mm" and model.path_of(8, 1024) == "mm"
 
 
+def test_split_rule_is_the_librarys():
+    """The model's copy of the split-K rule, which gives the partial results a projection writes and its consumer reads back,
+    against the library's (an internal function, found by its C++ name) over the shards, batches, formats and layouts."""
+    splits = getattr(psv.lib(), "_ZN3psv14gemm_sk_splitsEiiibbb")      # (batch, rows, columns, int8, tiled, pair)
+    splits.restype, splits.argtypes = C.c_int, [C.c_int] * 3 + [C.c_bool] * 3
+    shards = [(1024, 8, 8, 2816), (4096, 4, 1, 1792), (4096, 8, 2, 3584), (8192, 8, 1, 3584), (8192, 16, 2, 7168), (512, 4, 2, 256)]
+    for (hidden, nq, nkv, ffn), batch, fmt, layout in itertools.product(shards, range(1, 65), ("bf16", "int8"), ("row", "tiled")):
+        if model.path_of(batch, hidden, layout) == "vec":
+            continue
+        b = model.op_bytes(hidden, nq, nkv, ffn, batch, 100, weight_format=fmt, weight_layout=layout)
+        for name, rows, k in (("qkv", (nq + 2 * nkv) * 128, hidden), ("o", hidden, nq * 128), ("gate_up", 2 * ffn, hidden), ("down", hidden, ffn)):
+            want = splits(batch, rows, k, fmt == "int8", layout == "tiled", name == "gate_up")
+            assert b["p_" + name] == 8.0 * want * batch * rows, (hidden, batch, fmt, layout, name)
+
+
 def test_fit_line_recovers_a_line_and_refuses_nonsense():
     icpt, bw = model.fit_line([(1e6, 3.0 + 1e6 / 4e6), (8e6, 3.0 + 8e6 / 4e6), (30e6, 3.0 + 30e6 / 4e6)])
     assert icpt == pytest.approx(3.0) and bw == pytest.approx(4e6)
@@ -58,7 +76,7 @@ import json
 import os
 
 GOLDEN = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "measured_mi355x.json")
-TOL = 0.12      # relative error allowed per row and mode (worst: 9.2 %, batch 64 at 4k tokens; c1: 9.1 %)
+TOL = 0.12      # relative error allowed per row and mode (worst: 8.4 %, batch 64 at 4k tokens; c1: 5.8 %)
 
 
 def _golden():
