@@ -284,9 +284,12 @@ __global__ __launch_bounds__(64) void k_attn_prep(AttnPrepArgs a)
 }
 
 // Who appends: this kernel, which has the rows at hand; but its end waits for the value rows' 2-byte stores, one into every
-// channel, so that from batch 17 on a bf16 cache's rows are left to the attention, which has the time for them (70B-shaped
-// TP=8, batch 32, 32k tokens: 854 -> 847 us for four layers; TP=4, batch 64: 788 -> 778; batch 5 and 8 the other way round,
-// 643 / 637).  The larger batch also takes pieces of four channels: half the waves.
+// channel, so that a larger bf16 batch's rows are left to the attention, which has the time for them, and the sums are taken in
+// pieces of four channels: half the waves.  Measured here / there, us a layer, no windows: one kv head, 1k tokens, batch 5 70.2 /
+// 71.5, 8 71.0 / 72.1, 12 72.8 / 73.9, 16 73.4 / 74.3, 17 77.6 / 78.6, 24 80.0 / 81.1, 32 83.0 / 83.3, 64 103.3 / 103.3; 8k tokens,
+// 16 85.7 / 85.9, 24 97.4 / 97.2, 32 105.7 / 105.3; two kv heads, 12 108.3 / 109.8, 16 111.4 / 111.5, 24 122.5 / 122.4, 32 127.9 /
+// 127.4, 64 160.6 / 160.0.  The two meet between batch 16 and 32, later with fewer kv heads and shorter sequences; the line is at
+// the end of a batch tile.
 static bool prep_appends(const KvView &kv, int batch) { return kv.int8 || batch <= 16; }
 
 hipError_t launch_attn_prep(const float *part, int splits, const float2 *rope, KvView kv, int batch, int nq, int nkv, float *qkv,

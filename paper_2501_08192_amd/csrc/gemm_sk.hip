@@ -899,7 +899,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob
 }
 
 // Number of K splits, from a small cost model of the kernel.  More splits shorten the walk and cost partial traffic of
-// batch * N * 8 bytes each; small matrices end up with 8-16 splits, wide ones with as many as keep every CU busy.
+// batch * N * 8 bytes each.  On the 8B- and 70B-shaped shards that gives QKV 12-16 splits (96-240 workgroups of the chip's
+// 256 CUs; kSkMaxSplits caps the narrow ones), O and down 4-8 (128-256), gate | up 4-16 (224-512).
 //
 // One matrix, bf16 weights (QKV, O, down): a CU is as fast with one workgroup as with two (the two share its matrix cores,
 // LDS and memory pipeline; measured at batch 64, 117 MB: 256 workgroups of 28 slabs 30.7 us, 512 of 14 32.8, 448 of 16 33.2,
@@ -911,8 +912,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob
 // Gate | up (pair) and int8 weights: a workgroup needs ~0.6 us per slab it walks (latency of one pipelined slab step), 512
 // workgroups are resident at a time, and weights plus partial results stream at ~4 TB/s.  The pair keeps it because the
 // share of its range that a workgroup holds on chip through a communication window depends on short ranges
-// (gemm_sk_can_wait), and without one 224 workgroups and 448 measured the same (50.1 us, 235 MB at batch 64); int8 ranges
-// are half the bytes per slab, bound by latency, and want the second workgroup.
+// (gemm_sk_can_wait), and without one 224 workgroups and 448 measured the same (50.1 us, 235 MB at batch 64).  int8 weights keep
+// it for the larger batches: kernel times with at most 256 workgroups against 512 are, batch 64 of the 70B-shaped shards, QKV
+// 13.1 / 11.9 us, down 16.5 / 16.4 and 24.8 / 24.3, batch 39 down 14.5 / 13.7.  Up to one batch tile it is not the better rule:
+// batch 8 O 5.7 / 6.4 us, batch 16 O 6.2 / 7.2 and down 9.3 / 9.9, batch 5 of the 8B-shaped shard down 5.7 / 7.2.
 int gemm_sk_splits(int batch, int N, int K, bool w8, bool tiled, bool pair)
 {
     const int n_slabs = K / 64;
