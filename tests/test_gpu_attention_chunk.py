@@ -1,7 +1,7 @@
 """A chunk size set for all sequences (psv_set_attention_chunk): the matrix-core path's attention without the work list of the
 step's lengths, which a step takes by itself only where the list does not fit or tuning has chosen so.  Against the CPU oracle
 (tolerances of test_gpu_parity and test_gpu_int8; every byte of the cache outside the new rows untouched) for each cache, on both
-sides of the rule that says which kernel appends the new rows (batch 16 and 17), with lengths that leave chunks empty and new
+sides of the rule that says which kernel appends the new rows (batch 16 and 17), and on the vector path (batch 2), with lengths that leave chunks empty and new
 rows in a wave's first tile and beyond it.  A sequence's bits depend on the sequence alone then."""
 import numpy as np
 import pytest
@@ -69,7 +69,7 @@ def check_against_oracle(s, lens):
     return got
 
 
-@pytest.mark.parametrize("batch", [3, 16, 17])
+@pytest.mark.parametrize("batch", [2, 3, 16, 17])
 @pytest.mark.parametrize("cache", sorted(CACHES))
 def test_uniform_chunks_match_oracle(cache, batch):
     w = workload(cache, batch)
