@@ -315,7 +315,7 @@ psv_status psv_tune_attention(psv_ctx *c, const float *x_in, float *x_out, uint3
     // The steps of a candidate are enqueued behind a wait that outlasts their enqueueing, so that the device and not the host is timed;
     // a candidate's time is its faster one of two passes, the first of which also wakes the device.  (Enqueued into an idle queue,
     // the candidate that came first was measured at 57-90 us for a step that takes 44.)
-    const float wait_us = 600.f;
+    const float wait_us = 1500.f;
     c->attn_tuning = true;
     for (int pass = 0; pass < 2; ++pass)
         for (int k = 0; k < n_cand && st == PSV_OK; ++k) {

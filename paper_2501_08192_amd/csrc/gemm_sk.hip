@@ -913,8 +913,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob
 // workgroups are resident at a time, and weights plus partial results stream at ~4 TB/s.  The pair keeps it because the
 // share of its range that a workgroup holds on chip through a communication window depends on short ranges
 // (gemm_sk_can_wait), and without one 224 workgroups and 448 measured the same (50.1 us, 235 MB at batch 64).  int8 weights keep
-// it for the larger batches: kernel times with at most 256 workgroups against 512 are, batch 64 of the 70B-shaped shards, QKV
-// 13.1 / 11.9 us, down 16.5 / 16.4 and 24.8 / 24.3, batch 39 down 14.5 / 13.7.  Up to one batch tile it is not the better rule:
+// it for the larger batches: kernel times with at most 256 workgroups against this rule's 448-512 are, batch 64 of the 70B-shaped
+// shards, down 16.5 / 16.0 us and 24.8 / 24.3, batch 39 down 14.5 / 13.6.  Up to one batch tile it is not the better rule:
 // batch 8 O 5.7 / 6.4 us, batch 16 O 6.2 / 7.2 and down 9.3 / 9.9, batch 5 of the 8B-shaped shard down 5.7 / 7.2.
 int gemm_sk_splits(int batch, int N, int K, bool w8, bool tiled, bool pair)
 {
