@@ -171,6 +171,9 @@ __device__ __forceinline__ void two_digits(float t, float &m1, float &m2)
     m2 = fmaf(r, 254.0f, kMagic);
 }
 
+// 254 * D1 + D2 of a pair of exact digit sums, |D1| < 2^23: one 24-bit multiply-add
+__device__ __forceinline__ int mad_digits(int d1, int d2) { return __mul24(d1, 254) + d2; }
+
 // Maximum over aligned groups of 32 lanes, returned in every lane of the group (all lanes must be active).
 template <int CTRL>
 __device__ __forceinline__ float dpp_max(float v)

@@ -577,10 +577,14 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
 // The same split-K projection for int8 weights, entirely on the int8 matrix cores: the weight codes are the A
 // operand as they are (16 bytes = 16 consecutive k of one row per lane and 64-element slab), the activations
 // arrive as two int8 digit planes with one scale per 128-element block (store_digits4) and are the B operand.
-// Each digit has its own exact i32 accumulator; at the end of every 128-element block (two slabs) the pair is
-// folded into the fp32 accumulator as scale/254 * (254*D1 + D2).  No per-element conversion of weights anywhere.
-// (128-element slabs, i.e. whole 128-byte lines per row and step, measured slower: 19.6 -> 25 us on the 70B-shaped
-// gate/up matrix at batch 8.)
+// Each digit has its own exact i32 sum; a step is one block (two slabs: whole 128-byte lines of weights and activations, one
+// scale, one barrier), at whose end the pair is folded into the fp32 accumulator as scale/254 * (254*D1 + D2).  No per-element
+// conversion of weights anywhere.  The fold is a 24-bit multiply-add (|D1| <= 127 * 127 * 128 < 2^23): left to itself the compiler
+// takes the 64-bit one, an eighth of the rate and two moves for its wide addend, and the first product of a block starts from
+// the constant zero instead of cleared registers: 166 vector instructions a block and wave at three batch tiles where two
+// 64-element steps took 295.  Bound by the latency of its steps (a range of n blocks takes 2.5 us + n times 0.35 us at one batch
+// tile, 0.8 at four, far from 5 TB/s).  Steps of 64 elements -> blocks, same splits: 117 MB gate | up at batch 64 40.6 -> 33.9 us, 59 MB
+// at batch 8 14.5 -> 12.7, 29 MB at batch 39 13.8 -> 12.8, 29 MB down at batch 8 7.6 -> 6.2.
 struct GemmI8Args {
     const int8_t *W, *W2;          // rows >= split_row come from W2
     const float *scale, *scale2;   // per-row weight scales
@@ -588,39 +592,40 @@ struct GemmI8Args {
     const uint8_t *xd;             // digit plane d1 [round_up(batch,16)][K]; d2 x_plane bytes later; then the block scales
     size_t x_plane;
     float *part;                   // [splits][batch][N]
-    int batch, N, K, n_slabs, slabs_per_block;
+    int batch, N, K, n_blocks, blocks_per_wg;
     const float *ssq;              // see GemmSkArgs
     float eps;
     int tiled;                     // see GemmSkArgs; the unit of (row tile, slab) is 8 KiB: [wave][row group][lane][16 codes]
     SkWaitArgs wt;                 // k_gemm_sk_i8<1, HOLD>, HOLD > 0
 };
 
-constexpr int kSkI8Blocks = 66;    // 128-element blocks a workgroup's K range can touch (ranges of up to 128 slabs)
+constexpr int kSkI8Blocks = 18;    // most 128-element blocks of a waiting workgroup (gemm_sk_splits)
 
-// HOLD, pj: as for k_gemm_sk.  The waiting variant keeps the 8 slabs of its register ring, or those and 4 more in LDS
-// (8 KiB each), on chip.  The operand's block scales share cache lines between producer workgroups of different XCDs,
+// HOLD, pj: as for k_gemm_sk.  The waiting variant keeps the 4 blocks of its register ring, or those and 2 more in LDS
+// (16 KiB each), on chip.  The operand's block scales share cache lines between producer workgroups of different XCDs,
 // so the waiting variant reads those of its K range with device-coherent loads, once, after the wait.
 template <int NB, int HOLD>
-__global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob pj)
+__global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob pj)
 {
     constexpr bool WAIT = HOLD > 0;
     static_assert(!WAIT || NB == 1, "the waiting variant is built for one batch tile");
-    constexpr int PF = NB <= 2 ? 8 : 4;            // slabs of weight codes in flight per wave (2 x 16 bytes each); what two workgroups' registers hold
-    __shared__ uint4 xs[2][NB * 2][64];            // [buffer][batch tile * 2 + digit][lane ^ 2 * segment]: bank spread as in k_gemm_sk
-    __shared__ float bs[2][NB * 16];               // block scale of each batch row for the buffered slab
+    constexpr int PF = 4;                          // blocks of weight codes in flight per wave (4 x 16 bytes each)
+    __shared__ uint4 xs[2][NB * 4][64];            // [buffer][(batch tile * 2 + digit) * 2 + slab][lane ^ segment]: bank spread as in k_gemm_sk
+    __shared__ float bs[2][256];                   // block scale of each batch row for the buffered block (threads past the rows repeat the last)
     __shared__ float inv_s[NB * 16];
     __shared__ float bsl[WAIT ? 16 * kSkI8Blocks : 1];     // waiting variant: block scales of this K range, [batch row][block]
     __shared__ float ssq_s[WAIT ? kSkWaitEntries : 1];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, i = lane & 15, g = lane >> 4;
     const int row_base = blockIdx.x * 128 + w * 32;
-    const int s0 = blockIdx.y * a.slabs_per_block, s1 = min(s0 + a.slabs_per_block, a.n_slabs);
+    const int k0 = blockIdx.y * a.blocks_per_wg, k1 = min(k0 + a.blocks_per_wg, a.n_blocks);       // blocks of this range
     const int K = a.K;
     const float *bscale = reinterpret_cast<const float *>(a.xd + 2 * a.x_plane);
-    const int nblk128 = K / 128;
+    const int nblk128 = a.n_blocks;
 
     const int8_t *wp[2];
     bool wok[2];
-    const size_t wstep = a.tiled ? 8192 : 64;       // bytes from one slab to the next
+    const size_t wstep = a.tiled ? 16384 : 128;     // bytes from one block to the next
+    const int wslab = a.tiled ? 8192 : 64;          // ... from its first slab to its second
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
         const int r = row_base + mt * 16 + i;
@@ -635,107 +640,101 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob
         }
     }
     // Lane (i, g) owns bytes g*16 .. g*16+15 of row i of every 64-element slab: the A operand of one MFMA.
-    struct WFrag { uint4 c[2]; };
-    auto load_w = [&](int s, WFrag &f) {       // unpredicated: a row past N reads row 0 (wp) and is never stored
+    struct WFrag { uint4 c[2][2]; };           // [slab][row group]
+    auto load_w = [&](int k, WFrag &f) {       // unpredicated: a row past N reads row 0 (wp) and is never stored
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) f.c[mt] = ld16(reinterpret_cast<const uint16_t *>(wp[mt] + (size_t)s * wstep));
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) f.c[h][mt] = ld16(reinterpret_cast<const uint16_t *>(wp[mt] + (size_t)k * wstep + h * wslab));
     };
-    // activation slab: NB*128 16-byte units, unit u = ((tile*2 + digit)*16 + row)*4 + segment; 256 units are two tiles, so one
-    // 32-bit offset from uniform bases serves all loads of a thread (see k_gemm_sk)
-    constexpr int NU = (NB + 1) / 2;
-    struct SlabRegs { uint4 r[NU]; float sc; };
-    const uint32_t x_off = (uint32_t)((size_t)((tid >> 6) & 1) * a.x_plane + (size_t)((tid >> 7) * 16 + ((tid >> 2) & 15)) * K + (tid & 3) * 16);
-    const uint32_t s_off = (uint32_t)(tid * nblk128 * 4);
-    auto load_slab = [&](int s, SlabRegs &sr) {
+    // activation block: NB*256 16-byte units, unit u = ((tile*2 + digit)*16 + row)*8 + segment: a thread has the same digit, row and
+    // segment of every tile, one 32-bit offset from uniform bases serves all its loads (see k_gemm_sk)
+    struct BlockRegs { uint4 r[NB]; float sc; };
+    const uint32_t x_off = (uint32_t)((size_t)(tid >> 7) * a.x_plane + (size_t)((tid >> 3) & 15) * K + (tid & 7) * 16);
+    // No predicate on the scales: behind a branch in the loop the compiler sinks the folds of all four steps of a round past it,
+    // with every step's sums kept (256 registers and hundreds of spills instead of 150).
+    const int s_row = min(tid, NB * 16 - 1);
+    const uint32_t s_off = (uint32_t)(s_row * nblk128 * 4);
+    auto load_x = [&](int k, BlockRegs &br) {
 #pragma unroll
-        for (int j = 0; j < NU; ++j)
-            sr.r[j] = tid + j * 256 < NB * 128 ? ld16(reinterpret_cast<const uint16_t *>(a.xd + ((size_t)j * 32 * K + (size_t)s * 64) + x_off)) : zero16();
-        if (WAIT) sr.sc = tid < a.batch ? bsl[tid * kSkI8Blocks + (s >> 1) - (s0 >> 1)] : 0.f;
-        else sr.sc = tid < NB * 16 ? *reinterpret_cast<const float *>(reinterpret_cast<const char *>(bscale + (s >> 1)) + s_off) : 0.f;
+        for (int j = 0; j < NB; ++j) br.r[j] = ld16(reinterpret_cast<const uint16_t *>(a.xd + ((size_t)j * 16 * K + (size_t)k * 128) + x_off));
+        if (WAIT) br.sc = bsl[s_row * kSkI8Blocks + k - k0];
+        else br.sc = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(bscale + k) + s_off);
     };
-    const int x_slot = ((tid & 3) * 16 + ((tid >> 2) & 15)) ^ (2 * (tid & 3)), x_frag = (tid >> 7) * 2 + ((tid >> 6) & 1);
-    auto store_slab = [&](int buf, const SlabRegs &sr) {
+    const int x_seg = tid & 7, x_slot = ((x_seg & 3) * 16 + ((tid >> 3) & 15)) ^ x_seg, x_frag = (tid >> 7) * 2 + (x_seg >> 2);
+    auto store_x = [&](int buf, const BlockRegs &br) {
 #pragma unroll
-        for (int j = 0; j < NU; ++j)
-            if (tid + j * 256 < NB * 128) xs[buf][j * 4 + x_frag][x_slot] = sr.r[j];   // B operand: lane (row, segment)
-        if (tid < NB * 16) bs[buf][tid] = sr.sc;
+        for (int j = 0; j < NB; ++j) xs[buf][j * 4 + x_frag][x_slot] = br.r[j];        // B operand: lane (row, segment)
+        bs[buf][tid] = br.sc;
     };
     f32x4 acc[2][NB];
-    i32x4 d1[2][NB], d2[2][NB];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-        for (int n = 0; n < NB; ++n) {
-            acc[mt][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-            d1[mt][n] = i32x4{0, 0, 0, 0};
-            d2[mt][n] = i32x4{0, 0, 0, 0};
-        }
+        for (int n = 0; n < NB; ++n) acc[mt][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Waiting variant: see k_gemm_sk.  The ring's PF slabs and the LH after them stay on chip.
-    constexpr int LH = HOLD == 2 ? 4 : 0;
+    // Waiting variant: see k_gemm_sk.  The ring's PF blocks and the LH after them stay on chip.
+    constexpr int LH = HOLD == 2 ? 2 : 0;
     constexpr int HS = PF + LH;
-    __shared__ uint4 wl[LH ? LH * 2 * 256 : 1];
-    const bool held = WAIT && s1 - s0 >= HS;
+    __shared__ uint4 wl[LH ? LH * 4 * 256 : 1];
+    const bool held = WAIT && k1 - k0 >= HS;
     if (WAIT && (pj.n_regions || pj.kv_count))
         prefetch_walk(pj, blockIdx.y * gridDim.x + blockIdx.x, (uint64_t)gridDim.x * gridDim.y);
     if (held) {
-        {   // this workgroup's own slabs beyond the ones kept on chip: eight slabs (16 loads per lane) in flight, dropped
-            const int t_end = min(s1, s0 + (row_base < a.split_row ? a.wt.touch_w : a.wt.touch_w2));
+        {   // this workgroup's own blocks beyond the ones kept on chip: four blocks (16 loads per lane) in flight, dropped
+            const int t_end = min(k1, k0 + (row_base < a.split_row ? a.wt.touch_w : a.wt.touch_w2));
             uint32_t sink = 0;
-            for (int s = s0 + HS; s < t_end; s += 8) {
-                WFrag t[8];
+            for (int k = k0 + HS; k < t_end; k += 4) {
+                WFrag t[4];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    if (s + q < t_end) load_w(s + q, t[q]);
-                    else t[q].c[0] = t[q].c[1] = zero16();
+                for (int q = 0; q < 4; ++q) {
+                    if (k + q < t_end) load_w(k + q, t[q]);
+                    else t[q].c[0][0] = t[q].c[0][1] = t[q].c[1][0] = t[q].c[1][1] = zero16();
                 }
 #pragma unroll
-                for (int q = 0; q < 8; ++q) sink ^= xor4(t[q].c[0]) ^ xor4(t[q].c[1]);
+                for (int q = 0; q < 4; ++q) sink ^= xor4(t[q].c[0][0]) ^ xor4(t[q].c[0][1]) ^ xor4(t[q].c[1][0]) ^ xor4(t[q].c[1][1]);
             }
             asm volatile("" ::"v"(sink));
         }
+        if constexpr (LH > 0) {
+            WFrag t[LH];
 #pragma unroll
-        for (int e = 0; e < LH; e += 2) {
-            WFrag t[2];
-            load_w(s0 + PF + e, t[0]);
-            load_w(s0 + PF + e + 1, t[1]);
+            for (int e = 0; e < LH; ++e) load_w(k0 + PF + e, t[e]);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                uint4 *d = wl + ((e + j) * 2) * 256 + tid;
-                d[0] = t[j].c[0]; d[256] = t[j].c[1];
+            for (int e = 0; e < LH; ++e) {
+                uint4 *d = wl + (e * 4) * 256 + tid;
+                d[0] = t[e].c[0][0]; d[256] = t[e].c[0][1]; d[512] = t[e].c[1][0]; d[768] = t[e].c[1][1];
             }
         }
     }
     WFrag wq[PF];
 #pragma unroll
     for (int q = 0; q < PF; ++q)
-        if (!WAIT || s0 + q < s1) load_w(min(s0 + q, s1 - 1), wq[q]);
+        if (!WAIT || k0 + q < k1) load_w(min(k0 + q, k1 - 1), wq[q]);
     if (WAIT) {
-        if (w == 0) sk_wait_for_operand(a.wt, a.batch, K, s0, s1, lane);     // one wave polls
+        if (w == 0) sk_wait_for_operand(a.wt, a.batch, K, 2 * k0, 2 * k1, lane);     // one wave polls
         __syncthreads();
-        const int b0 = s0 >> 1, nbk = ((s1 - 1) >> 1) - b0 + 1;             // <= kSkI8Blocks
+        const int nbk = k1 - k0;                                            // <= kSkI8Blocks
         for (int idx = tid; idx < a.batch * nbk; idx += 256) {
             float v;
-            asm volatile("global_load_dword %0, %1, off sc0 sc1" : "=v"(v) : "v"(bscale + (size_t)(idx / nbk) * nblk128 + b0 + idx % nbk) : "memory");
-            asm volatile("s_waitcnt vmcnt(0)" : "+v"(v) : : "memory");
+            asm volatile("global_load_dword %0, %1, off sc0 sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(bscale + (size_t)(idx / nbk) * nblk128 + k0 + idx % nbk) : "memory");
             bsl[(idx / nbk) * kSkI8Blocks + idx % nbk] = v;
         }
         __syncthreads();
     }
-    // as many activation slabs as weight slabs in flight (see k_gemm_sk): 15 MB of gate/up at batch 39 17.2 -> 14.9 us
-    constexpr int XD = WAIT ? 2 : PF;
-    SlabRegs xr[XD];
-    constexpr int XG = WAIT ? 6 : 1;        // activation slabs requested ahead in the held part (see k_gemm_sk)
-    SlabRegs xa[XG];
+    // as many activation blocks as weight blocks in flight (see k_gemm_sk)
+    constexpr int XD = WAIT ? 1 : PF;
+    BlockRegs xr[XD];
+    constexpr int XG = WAIT ? 3 : 1;        // activation blocks requested ahead in the held part (see k_gemm_sk)
+    BlockRegs xa[XG];
     if (held) {
 #pragma unroll
-        for (int h = 0; h < XG; ++h) load_slab(s0 + h, xa[h]);
-        load_slab(min(s0 + HS, s1 - 1), xr[0]);
-        load_slab(min(s0 + HS + 1, s1 - 1), xr[1]);
+        for (int h = 0; h < XG; ++h) load_x(k0 + h, xa[h]);
+        load_x(min(k0 + HS, k1 - 1), xr[0]);
     } else {
 #pragma unroll
-        for (int q = 0; q < XD; ++q) load_slab(min(s0 + q, s1 - 1), xr[q]);
-        store_slab(0, xr[0]);
+        for (int q = 0; q < XD; ++q) load_x(min(k0 + q, k1 - 1), xr[q]);
+        store_x(0, xr[0]);
     }
     auto inv_rms = [&]() {      // 1/rms of every batch row (see k_gemm_sk)
         if (tid < NB * 16) {
@@ -766,105 +765,96 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob
     if (!WAIT) inv_rms();
     __syncthreads();
 
-    // one slab: both digit planes against the weight codes; at the end of a 128-element block (or of the range) the pair
-    // of exact sums is folded into the fp32 accumulator
-    const int x_lane = lane ^ (2 * g);
-    auto mfma_slab = [&](int s, int buf, const WFrag &f) {
-        const bool fold = (s & 1) || s + 1 == s1;
+    // one block: both digit planes against the weight codes, then the pair of exact sums goes into the fp32 accumulator
+    const int l0 = lane ^ g, l1 = lane ^ g ^ 4;
+    auto mfma_block = [&](int buf, const WFrag &f) {
 #pragma unroll
         for (int n = 0; n < NB; ++n) {
-            const i32x4 x1 = __builtin_bit_cast(i32x4, xs[buf][n * 2 + 0][x_lane]);
-            const i32x4 x2 = __builtin_bit_cast(i32x4, xs[buf][n * 2 + 1][x_lane]);
+            const i32x4 a0 = __builtin_bit_cast(i32x4, xs[buf][(n * 2 + 0) * 2 + 0][l0]), a1 = __builtin_bit_cast(i32x4, xs[buf][(n * 2 + 0) * 2 + 1][l1]);
+            const i32x4 b0 = __builtin_bit_cast(i32x4, xs[buf][(n * 2 + 1) * 2 + 0][l0]), b1 = __builtin_bit_cast(i32x4, xs[buf][(n * 2 + 1) * 2 + 1][l1]);
+            const float sc = bs[buf][n * 16 + i] * (1.0f / 254.0f);
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt) {
-                const i32x4 wc = __builtin_bit_cast(i32x4, f.c[mt]);
-                d1[mt][n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wc, x1, d1[mt][n], 0, 0, 0);
-                d2[mt][n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wc, x2, d2[mt][n], 0, 0, 0);
-            }
-            if (fold) {
-                const float sc = bs[buf][n * 16 + i] * (1.0f / 254.0f);
+                const i32x4 z = {0, 0, 0, 0}, w0 = __builtin_bit_cast(i32x4, f.c[0][mt]), w1 = __builtin_bit_cast(i32x4, f.c[1][mt]);
+                i32x4 d1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(w0, a0, z, 0, 0, 0);
+                i32x4 d2 = __builtin_amdgcn_mfma_i32_16x16x64_i8(w0, b0, z, 0, 0, 0);
+                d1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(w1, a1, d1, 0, 0, 0);
+                d2 = __builtin_amdgcn_mfma_i32_16x16x64_i8(w1, b1, d2, 0, 0, 0);
 #pragma unroll
-                for (int mt = 0; mt < 2; ++mt) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        acc[mt][n][j] = fmaf(sc, (float)(d1[mt][n][j] * 254 + d2[mt][n][j]), acc[mt][n][j]);
-                    d1[mt][n] = i32x4{0, 0, 0, 0};
-                    d2[mt][n] = i32x4{0, 0, 0, 0};
-                }
+                for (int j = 0; j < 4; ++j) acc[mt][n][j] = fmaf(sc, (float)mad_digits(d1[j], d2[j]), acc[mt][n][j]);
             }
         }
     };
 
-    int sb0 = s0;
-    if (held) {     // the slabs held on chip, in the order of the range; ring slots are refilled with the slab HS further on
+    int kb = k0;
+    if (held) {     // the blocks held on chip, in the order of the range; ring slots are refilled with the block HS further on
 #pragma unroll
         for (int h = 0; h < HS; ++h) {
             const int buf = h & 1;
-            store_slab(buf, xa[h % XG]);
-            if (h + XG < HS) load_slab(s0 + h + XG, xa[h % XG]);
+            store_x(buf, xa[h % XG]);
+            if (h + XG < HS) load_x(k0 + h + XG, xa[h % XG]);
             __syncthreads();
             if (h < PF) {
-                mfma_slab(s0 + h, buf, wq[h]);
-                load_w(min(s0 + h + HS, s1 - 1), wq[h]);
+                mfma_block(buf, wq[h]);
+                load_w(min(k0 + h + HS, k1 - 1), wq[h]);
             } else {
                 WFrag f;
-                const uint4 *d = wl + ((h - PF) * 2) * 256 + tid;
-                f.c[0] = d[0]; f.c[1] = d[256];
-                mfma_slab(s0 + h, buf, f);
+                const uint4 *d = wl + ((h - PF) * 4) * 256 + tid;
+                f.c[0][0] = d[0]; f.c[0][1] = d[256]; f.c[1][0] = d[512]; f.c[1][1] = d[768];
+                mfma_block(buf, f);
             }
         }
-        sb0 = s0 + HS;
-        if (sb0 < s1) store_slab(0, xr[0]);     // HS is even: the main loop's first slab goes to buffer 0
+        kb = k0 + HS;
+        if (kb < k1) store_x(0, xr[0]);         // HS is even: the main loop's first block goes to buffer 0
         __syncthreads();
     }
     // straight-line rounds, then the end of the range: see k_gemm_sk
-    int sb = sb0;
-    for (; sb + 2 * PF <= s1; sb += PF) {
+    for (; kb + 2 * PF <= k1; kb += PF) {
 #pragma unroll
         for (int q = 0; q < PF; ++q) {
-            const int s = sb + q, buf = q & 1;      // (s - s0) & 1, because PF and the number of slabs held are even
-            load_slab(s + XD, xr[q % XD]);
-            mfma_slab(s, buf, wq[q]);
-            load_w(s + PF, wq[q]);
-            store_slab(buf ^ 1, xr[(q + 1) % XD]);
+            const int k = kb + q, buf = q & 1;      // (k - k0) & 1, because PF and the number of blocks held are even
+            load_x(k + XD, xr[q % XD]);
+            mfma_block(buf, wq[q]);
+            load_w(k + PF, wq[q]);
+            store_x(buf ^ 1, xr[(q + 1) % XD]);
             __syncthreads();
         }
     }
     if constexpr (WAIT) {
-        for (; sb < s1; sb += PF) {                 // the last rounds: every step checks what is left
+        for (; kb < k1; kb += PF) {                 // the last rounds: every step checks what is left
 #pragma unroll
             for (int q = 0; q < PF; ++q) {
-                const int s = sb + q;
-                if (s < s1) {                       // uniform over the workgroup
+                const int k = kb + q;
+                if (k < k1) {                       // uniform over the workgroup
                     const int buf = q & 1;
-                    if (s + XD < s1) load_slab(s + XD, xr[q % XD]);
-                    mfma_slab(s, buf, wq[q]);
-                    if (s + PF < s1) load_w(s + PF, wq[q]);
-                    if (s + 1 < s1) store_slab(buf ^ 1, xr[(q + 1) % XD]);
+                    if (k + XD < k1) load_x(k + XD, xr[q % XD]);
+                    mfma_block(buf, wq[q]);
+                    if (k + PF < k1) load_w(k + PF, wq[q]);
+                    if (k + 1 < k1) store_x(buf ^ 1, xr[(q + 1) % XD]);
                     __syncthreads();
                 }
             }
         }
     } else {
-        if (sb + PF < s1) {                         // refills partly past the range
+        if (kb + PF < k1) {                         // refills partly past the range
 #pragma unroll
             for (int q = 0; q < PF; ++q) {
-                const int s = sb + q, buf = q & 1;
-                load_slab(min(s + XD, s1 - 1), xr[q % XD]);
-                mfma_slab(s, buf, wq[q]);
-                load_w(min(s + PF, s1 - 1), wq[q]);
-                store_slab(buf ^ 1, xr[(q + 1) % XD]);
+                const int k = kb + q, buf = q & 1;
+                load_x(min(k + XD, k1 - 1), xr[q % XD]);
+                mfma_block(buf, wq[q]);
+                load_w(min(k + PF, k1 - 1), wq[q]);
+                store_x(buf ^ 1, xr[(q + 1) % XD]);
                 __syncthreads();
             }
-            sb += PF;
+            kb += PF;
         }
 #pragma unroll
         for (int q = 0; q < PF; ++q) {              // what is left is in registers
-            const int s = sb + q;
-            if (s < s1) {
+            const int k = kb + q;
+            if (k < k1) {
                 const int buf = q & 1;
-                mfma_slab(s, buf, wq[q]);
-                if (s + 1 < s1) store_slab(buf ^ 1, xr[(q + 1) % XD]);
+                mfma_block(buf, wq[q]);
+                if (k + 1 < k1) store_x(buf ^ 1, xr[(q + 1) % XD]);
                 __syncthreads();
             }
         }
@@ -909,26 +899,36 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob
 // 42 MB QKV at batch 64 16.9 -> 13.6 us, at batch 16 13.4 -> 11.9; 59 MB down at batch 32 15.6 -> 13.6; 33 MB O at
 // batch 16 10.3 -> 8.3; the down and O kernels' consumers read half the partials.
 //
-// Gate | up (pair) and int8 weights: a workgroup needs ~0.6 us per slab it walks (latency of one pipelined slab step), 512
+// int8 weights, every matrix: the same rule in blocks of 128 elements, 0.6 us each (one batch tile 0.35, four 0.8) and 1 us a
+// range for its first load and its partial result; within 0.4 us of the best of sixteen on the shards' matrices at batch 5-64.
+// Against filling 512 places, which it replaces: 15 MB down at batch 39 8.4 -> 7.4 us, 29 MB gate | up 12.8 -> 11.5; batch 8
+// 29 MB down 6.2 -> 6.0, 8 MB O 3.7 -> 3.2; batch 16 17 MB O 6.9 -> 5.1; batch 5 15 MB gate | up 7.8 -> 6.2, 7 MB down
+// 5.9 -> 4.2; batch 64 59 MB down 21.5 -> 19.0.  A range of the pair is at most 36 slabs, three times what a workgroup keeps on
+// chip through a window (gemm_sk_can_wait): longer ones are no faster on tiled weights (117 MB at batch 64 33.8 / 34.1 us) and
+// slower on row-major ones (batch 16 28.6 / 24.6).  Where the pair can be launched into its window and its workgroups are still
+// resident together, at most 18: the part that the window's end finds on chip counts for more than the walk (59 MB at batch 8,
+// 16 slabs a range or 32: 93.5 / 96.5 us a layer; without a window 12.2 / 12.3 us).
+//
+// Gate | up (pair) in bf16: a workgroup needs ~0.6 us per slab it walks (latency of one pipelined slab step), 512
 // workgroups are resident at a time, and weights plus partial results stream at ~4 TB/s.  The pair keeps it because the
 // share of its range that a workgroup holds on chip through a communication window depends on short ranges
-// (gemm_sk_can_wait), and without one 224 workgroups and 448 measured the same (50.1 us, 235 MB at batch 64).  int8 weights keep
-// it for the larger batches: kernel times with at most 256 workgroups against this rule's 448-512 are, batch 64 of the 70B-shaped
-// shards, down 16.5 / 16.0 us and 24.8 / 24.3, batch 39 down 14.5 / 13.6.  Up to one batch tile it is not the better rule:
-// batch 8 O 5.7 / 6.4 us, batch 16 O 6.2 / 7.2 and down 9.3 / 9.9, batch 5 of the 8B-shaped shard down 5.7 / 7.2.
+// (gemm_sk_can_wait), and without one 224 workgroups and 448 measured the same (50.1 us, 235 MB at batch 64).
 int gemm_sk_splits(int batch, int N, int K, bool w8, bool tiled, bool pair)
 {
     const int n_slabs = K / 64;
     const double row_groups = (double)((N + 127) / 128);
-    const double w_bytes = (w8 ? 1.0 : 2.0) * N * K, part_bytes = 8.0 * batch * N;
-    if (!w8 && !pair) {
+    const double w_bytes = 2.0 * N * K, part_bytes = 8.0 * batch * N;
+    if (w8 || !pair) {
+        const int step = w8 ? 2 : 1, n_steps = n_slabs / step;
+        const double walk = w8 ? 0.6 : 0.45, range = w8 ? 1.0 : 0.0;
+        const int longest = !pair ? n_slabs : batch <= 16 && row_groups * ((n_slabs + 17) / 18) <= 512 ? 18 : 36;
         int best = 1;
         double best_cost = 1e30;
         for (int ks = 1; ks <= kSkMaxSplits && ks * 2 <= n_slabs; ++ks) {
-            const int spb = (n_slabs + ks - 1) / ks;
-            if ((n_slabs + spb - 1) / spb != ks) continue;
+            const int steps = (n_steps + ks - 1) / ks;
+            if ((n_steps + steps - 1) / steps != ks || steps * step > longest) continue;
             const double fullest = (double)(((long long)row_groups * ks + 255) / 256);
-            const double cost = fullest * spb * 0.45 + ks * part_bytes / 5.0e6;
+            const double cost = fullest * (steps * walk + range) + ks * part_bytes / 5.0e6;
             if (cost < best_cost - 1e-9) { best_cost = cost; best = ks; }
         }
         return best;
@@ -955,6 +955,13 @@ int gemm_sk_splits(int batch, int N, int K, bool w8, bool tiled, bool pair)
 bool gemm_sk_supported(int batch, int N, int K)
 {
     return batch >= 1 && batch <= 64 && N % 16 == 0 && K % 64 == 0;
+}
+
+// slabs of a range: int8 weights are split in whole blocks of two slabs
+static int sk_range_slabs(int K, int splits, bool w8)
+{
+    const int step = w8 ? 128 : 64;
+    return (K / step + splits - 1) / splits * (step / 64);
 }
 
 // Which waiting variant a range of `slabs_per_block` slabs takes: the one that keeps 12 slabs on chip if the range has them.
@@ -1010,12 +1017,11 @@ bool gemm_sk_can_wait(int batch, int N, int K, bool w8, bool tiled, int cus)
     if (!r.ok) return false;
     const int splits = gemm_sk_splits(batch, N, K, w8, tiled, true);
     const int nb = (batch + 15) / 16;
-    const int kind = w8 ? 1 : nb == 2 ? 2 : 0, lv = sk_hold_level((K / 64 + splits - 1) / splits, nb) - 1;
+    const int kind = w8 ? 1 : nb == 2 ? 2 : 0, spb = sk_range_slabs(K, splits, w8), lv = sk_hold_level(spb, nb) - 1;
     const long long grid = (long long)((N + 127) / 128) * splits;
     // Worth it only if a good part of a workgroup's range stays on chip: with less than a third (two batch tiles on the
     // 235 MB gate/up matrix of a TP=4 70B-shaped shard: 8 slabs of 32) the wait's latencies cost more than the slabs save.
     {
-        const int spb = (K / 64 + splits - 1) / splits;
         const int hs = w8 ? (lv ? 12 : 8) : nb == 2 ? (lv ? 8 : 6) : (lv ? 12 : 6);
         if (hs * 3 < spb) return false;
     }
@@ -1031,15 +1037,15 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
                           int batch, int N, int K, const SkWait *wait, hipStream_t s)
 {
     const int nb = (batch + 15) / 16;
-    // planned share of each matrix, spread evenly over its workgroups: slabs of a workgroup's range that are either kept
-    // on chip or read and dropped
-    auto fill_wait = [&](SkWaitArgs &wt, int slabs_per_block) {
+    // planned share of each matrix, spread evenly over its workgroups: steps (slabs, int8: blocks of two) of a workgroup's range
+    // that are either kept on chip or read and dropped
+    auto fill_wait = [&](SkWaitArgs &wt, int steps) {
         wt.win_done = wait->win_done; wt.win_seq = wait->win_seq;
         wt.ll = static_cast<const uint2 *>(wait->ssq_ll); wt.ll_stride = (unsigned)sk_tag_stride(batch, K);
         wt.tag = wait->tag; wt.iters = wait->iters;
         wt.ticks = wait->ticks; wt.err = wait->err;
-        wt.touch_w = (int)(wait->share_w * slabs_per_block + 0.5);
-        wt.touch_w2 = (int)(wait->share_w2 * slabs_per_block + 0.5);
+        wt.touch_w = (int)(wait->share_w * steps + 0.5);
+        wt.touch_w2 = (int)(wait->share_w2 * steps + 0.5);
     };
     if (wait && (!ssq || !wait->ssq_ll || !wait->win_done || batch > (W.scale ? 16 : kSkWaitMaxBatch) || K % 512 || (long long)batch * (K / 512) > kSkWaitEntries)) return hipErrorInvalidValue;
     if (W.scale) {   // int8 weights: xb holds digit planes (bytes), see k_gemm_sk_i8
@@ -1047,15 +1053,15 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
         q.W = static_cast<const int8_t *>(W.w); q.W2 = static_cast<const int8_t *>(W2.w ? W2.w : W.w);
         q.scale = W.scale; q.scale2 = W2.w ? W2.scale : W.scale; q.split_row = W2.w ? split_row : N;
         q.xd = reinterpret_cast<const uint8_t *>(xb); q.x_plane = (size_t)nb * 16 * K;
-        q.part = part; q.batch = batch; q.N = N; q.K = K; q.n_slabs = K / 64; q.ssq = ssq; q.eps = eps;
+        q.part = part; q.batch = batch; q.N = N; q.K = K; q.n_blocks = K / 128; q.ssq = ssq; q.eps = eps;
         q.tiled = W.tiled ? 1 : 0;
         const int splits = gemm_sk_splits(batch, N, K, true, W.tiled, W2.w != nullptr);
-        q.slabs_per_block = (q.n_slabs + splits - 1) / splits;
+        q.blocks_per_wg = (q.n_blocks + splits - 1) / splits;
         const dim3 grid((N + 127) / 128, splits);
         if (wait) {
-            fill_wait(q.wt, q.slabs_per_block);
+            fill_wait(q.wt, q.blocks_per_wg);
             const PrefetchJob pj = wait->job ? *wait->job : PrefetchJob{};
-            if (sk_hold_level(q.slabs_per_block) == 2) PSV_LAUNCH((k_gemm_sk_i8<1, 2>), grid, dim3(256), 0, s, q, pj);
+            if (sk_hold_level(2 * q.blocks_per_wg) == 2) PSV_LAUNCH((k_gemm_sk_i8<1, 2>), grid, dim3(256), 0, s, q, pj);
             else PSV_LAUNCH((k_gemm_sk_i8<1, 1>), grid, dim3(256), 0, s, q, pj);
             return hipGetLastError();
         }

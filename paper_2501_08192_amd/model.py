@@ -78,21 +78,26 @@ def path_of(batch, hidden, weight_layout="row"):
 
 
 def sk_splits(batch, n_rows, k, weight_bytes=2.0, tiled=False, pair=True):
-    """K splits of the split-K GEMM: the library's own rule.  One matrix of bf16 weights (pair False: QKV, O, down): the fullest of
-    256 compute units walks ceil(workgroups / 256) ranges at 0.45 us a slab, partials at 5 TB/s.  The gate/up pair, and int8
-    weights: 0.6 us a slab, 512 resident workgroups, weights and partials at 4 TB/s."""
+    """K splits of the split-K GEMM: the library's own rule.  One matrix of bf16 weights (pair False: QKV, O, down), and int8
+    weights: the fullest of 256 compute units walks ceil(workgroups / 256) ranges at 0.45 us a slab (int8: 0.6 us a block of two and 1 us a
+    range; the pair's ranges of at most 36 slabs, 18 up to batch 16 where 512
+    places hold them), partials at 5 TB/s.  The gate/up pair in bf16: 0.6 us a slab, 512 resident
+    workgroups, weights and partials at 4 TB/s."""
     n_slabs = k // 64
     row_groups = (n_rows + 127) // 128
     w_bytes, part_bytes = weight_bytes * n_rows * k, 8.0 * batch * n_rows
-    single = weight_bytes == 2.0 and not pair
+    w8 = weight_bytes == 1.0
+    single, step = w8 or not pair, 2 if w8 else 1
+    longest = n_slabs if not (w8 and pair) else 18 if batch <= 16 and row_groups * ((n_slabs + 17) // 18) <= 512 else 36
     best, best_cost, best1, best1_cost = 1, 1e30, 0, 1e30
     for ks in range(1, min(16, n_slabs // 2) + 1):
-        spb = (n_slabs + ks - 1) // ks
-        if (n_slabs + spb - 1) // spb != ks:
+        steps = (n_slabs // step + ks - 1) // ks
+        spb = steps * step
+        if (n_slabs // step + steps - 1) // steps != ks or spb > longest:
             continue
         if single:
             rounds = (row_groups * ks + 255) // 256
-            cost = rounds * spb * 0.45 + ks * part_bytes / 5.0e6
+            cost = rounds * (steps * 0.6 + 1.0 if w8 else steps * 0.45) + ks * part_bytes / 5.0e6
         else:
             rounds = (row_groups * ks + 511) // 512
             cost = rounds * spb * 0.6 + (w_bytes + ks * part_bytes) / 4.0e6
@@ -117,7 +122,8 @@ def mm_hold(batch, hidden, ffn, weight_format="bf16", cus=256, weight_layout="ro
     nb = (batch + 15) // 16
     n_rows = 2 * ffn
     splits = sk_splits(batch, n_rows, hidden, 1.0 if w8 else 2.0, weight_layout == "tiled")
-    spb = (hidden // 64 + splits - 1) // splits
+    step = 2 if w8 else 1                   # int8 weights are split in whole blocks of two slabs
+    spb = (hidden // 64 // step + splits - 1) // splits * step
     grid = (n_rows + 127) // 128 * splits
     big = spb >= (12 if nb == 1 else 8)
     held = (12 if big else 8) if w8 else ((8 if big else 6) if nb == 2 else (12 if big else 6))
