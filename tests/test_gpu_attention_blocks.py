@@ -1,0 +1,37 @@
+"""A page-table entry outside the pool is a block of zeros: never followed, wherever in a wave's tiles it lies.  The same bits as with
+the entry pointing to a block that holds zeros, for chunks of one to six tiles a wave with ragged ends, on the vector and on the
+matrix-core path, for every cache format."""
+import pytest
+import torch
+
+from paper_2501_08192_amd import binding as psv
+from paper_2501_08192_amd import synth
+from paper_2501_08192_amd.harness import Session
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch", [1, 3, 17])
+@pytest.mark.parametrize("kv,layout", [("bf16", "head"), ("bf16", "token"), ("int8", "head")], ids=["bf16", "token", "int8"])
+@pytest.mark.parametrize("chunk", [0, 512, 1536])
+def test_entries_outside_the_pool_read_as_zeros(batch, kv, layout, chunk):
+    w = synth.Workload("blocks", 1, 512, 4, 2, 128, 256, batch, 1500, True, (0.0, 0.0), kv_format=kv, kv_layout=layout)
+    with Session(w, seed=17, pool_slack_blocks=1, fused=0) as s:
+        if chunk:
+            psv.psv_set_attention_chunk(s.ctx, chunk)
+        lens = torch.tensor([1500 - 83 * b for b in range(batch)], dtype=torch.int32)
+        s.seq_lens.copy_(lens)
+        used = s.page_table_host.reshape(-1).tolist()
+        spare = (set(range(s.pool_blocks)) - set(used)).pop()
+        s.k_pools[0][spare] = 0
+        s.v_pools[0][spare] = 0
+        outs = []
+        for wrong in ([spare] * 3, [-1, s.pool_blocks, 2 ** 31 - 1]):
+            table = s.page_table_host.clone()
+            for b in range(batch):
+                for n, lb in enumerate((0, 3, 7, 18, 33, 35, 36, 37, 64)):      # first and last block of a tile, a whole tile, single ones
+                    if lb != (int(lens[b]) - 1) // 16:                          # not the block that takes the new row
+                        table[b, lb] = wrong[(n + b) % 3]
+            s.page_table.copy_(table)
+            outs.append(s.run().clone())
+        assert torch.isfinite(outs[0]).all() and torch.equal(outs[0], outs[1])
