@@ -244,7 +244,7 @@ __device__ __forceinline__ uint32_t xor4(uint4 v) { return v.x ^ v.y ^ v.z ^ v.w
 // ranges are up to twice as long as a chip filled with two workgroups a CU would give it (gemm_sk_splits); gate | up keeps its
 // short ranges and the registers of its waiting form.  Distance of the QKV sums from 64 bits at 11 slabs a range: one sum 2.44e-7,
 // apart 1.73e-7 (eight slabs a range, one sum: 2.18e-7); a step takes as long either way.
-template <int NB, int HOLD, bool APART>
+template <int NB, int HOLD, bool APART, bool TURN = false>
 __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj)
 {
     constexpr bool WAIT = HOLD > 0;
@@ -260,6 +260,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
     const int row_base = blockIdx.x * 128 + w * 32;
     const int s0 = blockIdx.y * a.slabs_per_block, s1 = min(s0 + a.slabs_per_block, a.n_slabs);
     const int K = a.K;
+    // TURN: a range is walked from its slab `turn` on and round, see sk_turn
+    const int turn = TURN ? (int)(blockIdx.x * 2) % (s1 - s0) : 0;
+    auto slab = [&](int s) { return !TURN ? s : s + turn < s1 ? s + turn : s + turn - (s1 - s0); };
 
     // Lane (i, g) owns elements g*8 .. g*8+7 of both 32-element halves of row i of every 64-element slab (the matrix
     // cores' own operand order): each of its two load instructions covers 64 contiguous bytes of every row, whole
@@ -285,6 +288,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
     }
     struct WFrag { uint4 a0[2], a1[2]; };
     auto load_w = [&](int s, WFrag &f) {
+        s = slab(s);
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
             f.a0[mt] = wok[mt] ? ld16(wp[mt] + (size_t)s * wstep) : zero16();
@@ -292,6 +296,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
         }
     };
     auto load_w_all = [&](int s, WFrag &f) {   // unpredicated: a row past N reads row 0 (wp) and is never stored
+        s = slab(s);
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
             f.a0[mt] = ld16(wp[mt] + (size_t)s * wstep);
@@ -302,6 +307,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
     // and segment of every tile: one 32-bit offset from uniform bases serves all its loads (both planes are far below 4 GiB).
     const uint32_t x_off = (uint32_t)(((size_t)(tid >> 7) * a.x_plane + (size_t)((tid >> 3) & 15) * K + (tid & 7) * 8) * 2);
     auto load_slab = [&](int s, uint4 (&r)[NB]) {
+        s = slab(s);
 #pragma unroll
         for (int j = 0; j < NB; ++j)
             r[j] = ld16(reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(a.xb + ((size_t)j * 16 * K + (size_t)s * 64)) + x_off));
@@ -964,15 +970,24 @@ static int sk_range_slabs(int K, int splits, bool w8)
     return (K / step + splits - 1) / splits * (step / 64);
 }
 
+// Where the workgroups of a row-major matrix walk ranges that begin at multiples of 4 KiB of rows that do, all of them ask for the
+// same place within 4 KiB at the same time, a sixteenth of the memory channels.  There every row tile starts two slabs (256
+// bytes) further into its range than the one before: 235 MB gate | up, rows of 16 KiB, batch 16 56.1 -> 50.4 us (one slab 50.2, three
+// 49.7).  Other ranges spread by themselves and are walked in order (rows of 14 KiB 22.1 -> 23.4 with a turn, ranges of 15 slabs
+// no difference).  The tiled layout takes the same turn, so that a row's sums have one order in both; it is no slower for it (42.0
+// -> 40.8; with one slab 48.8).  Gate | up only, in kernels of its own: no single matrix of the shards has such ranges, and the wrap
+// costs the others up to 1 us (batch 16 O 7.9 -> 8.7).
+static bool sk_turn(int K, int slabs_per_block) { return K % 2048 == 0 && slabs_per_block % 32 == 0; }
+
 // Which waiting variant a range of `slabs_per_block` slabs takes: the one that keeps 12 slabs on chip if the range has them.
 static int sk_hold_level(int slabs_per_block, int nb = 1) { return slabs_per_block >= (nb == 1 ? 12 : 8) ? 2 : 1; }
 
-// Resources of the waiting variants ([bf16 | int8 | bf16 with two batch tiles][hold level - 1]) and of the kernel they wait for, asked from
+// Resources of the waiting variants ([bf16 | int8 | bf16 with two batch tiles | bf16 with a turn][hold level - 1]) and of the kernel they wait for, asked from
 // the runtime once.
 struct SkWaitRes {
-    int occ[3][2];       // resident workgroups per compute unit
-    int regs[3][2];      // registers per lane (vector + accumulation), rounded up to the allocation unit
-    int lds[3][2];       // static LDS bytes per workgroup
+    int occ[4][2];       // resident workgroups per compute unit
+    int regs[4][2];      // registers per lane (vector + accumulation), rounded up to the allocation unit
+    int lds[4][2];       // static LDS bytes per workgroup
     int regs_signal;     // k_resid_sum<true>
     bool ok;
 };
@@ -993,6 +1008,7 @@ static const SkWaitRes &sk_wait_res()
         };
         ask(0, 0, k_gemm_sk<1, 1, false>);
         ask(0, 1, k_gemm_sk<1, 2, false>);
+        ask(3, 1, k_gemm_sk<1, 2, false, true>);
         ask(1, 0, k_gemm_sk_i8<1, 1>);
         ask(1, 1, k_gemm_sk_i8<1, 2>);
         ask(2, 0, k_gemm_sk<2, 1, false>);
@@ -1017,7 +1033,8 @@ bool gemm_sk_can_wait(int batch, int N, int K, bool w8, bool tiled, int cus)
     if (!r.ok) return false;
     const int splits = gemm_sk_splits(batch, N, K, w8, tiled, true);
     const int nb = (batch + 15) / 16;
-    const int kind = w8 ? 1 : nb == 2 ? 2 : 0, spb = sk_range_slabs(K, splits, w8), lv = sk_hold_level(spb, nb) - 1;
+    const int spb = sk_range_slabs(K, splits, w8), lv = sk_hold_level(spb, nb) - 1;
+    const int kind = w8 ? 1 : nb == 2 ? 2 : sk_turn(K, spb) ? 3 : 0;
     const long long grid = (long long)((N + 127) / 128) * splits;
     // Worth it only if a good part of a workgroup's range stays on chip: with less than a third (two batch tiles on the
     // 235 MB gate/up matrix of a TP=4 70B-shaped shard: 8 slabs of 32) the wait's latencies cost more than the slabs save.
@@ -1082,18 +1099,21 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
     a.tiled = W.tiled ? 1 : 0;
     const int splits = gemm_sk_splits(batch, N, K, false, W.tiled, W2.w != nullptr);
     a.slabs_per_block = (a.n_slabs + splits - 1) / splits;
+    const bool turn = W2.w && sk_turn(K, a.slabs_per_block);
     const dim3 grid((N + 127) / 128, splits);
     if (wait) {
         fill_wait(a.wt, a.slabs_per_block);
         const PrefetchJob pj = wait->job ? *wait->job : PrefetchJob{};
         const int lv = sk_hold_level(a.slabs_per_block, nb);
-        if (nb == 1 && lv == 2) PSV_LAUNCH((k_gemm_sk<1, 2, false>), grid, dim3(256), 0, s, a, pj);
+        if (turn && nb != 1) return hipErrorInvalidValue;       // gemm_sk_can_wait: eight slabs are too little of such a range
+        if (turn) PSV_LAUNCH((k_gemm_sk<1, 2, false, true>), grid, dim3(256), 0, s, a, pj);
+        else if (nb == 1 && lv == 2) PSV_LAUNCH((k_gemm_sk<1, 2, false>), grid, dim3(256), 0, s, a, pj);
         else if (nb == 1) PSV_LAUNCH((k_gemm_sk<1, 1, false>), grid, dim3(256), 0, s, a, pj);
         else if (lv == 2) PSV_LAUNCH((k_gemm_sk<2, 2, false>), grid, dim3(256), 0, s, a, pj);
         else PSV_LAUNCH((k_gemm_sk<2, 1, false>), grid, dim3(256), 0, s, a, pj);
         return hipGetLastError();
     }
-    switch (W2.w ? nb : nb + 4) {        // one matrix: the planes' products summed apart
+    switch (turn ? nb + 8 : W2.w ? nb : nb + 4) {        // one matrix: the planes' products summed apart
     case 1: PSV_LAUNCH((k_gemm_sk<1, 0, false>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
     case 2: PSV_LAUNCH((k_gemm_sk<2, 0, false>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
     case 3: PSV_LAUNCH((k_gemm_sk<3, 0, false>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
@@ -1102,6 +1122,10 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
     case 6: PSV_LAUNCH((k_gemm_sk<2, 0, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
     case 7: PSV_LAUNCH((k_gemm_sk<3, 0, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
     case 8: PSV_LAUNCH((k_gemm_sk<4, 0, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    case 9: PSV_LAUNCH((k_gemm_sk<1, 0, false, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    case 10: PSV_LAUNCH((k_gemm_sk<2, 0, false, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    case 11: PSV_LAUNCH((k_gemm_sk<3, 0, false, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    case 12: PSV_LAUNCH((k_gemm_sk<4, 0, false, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
