@@ -55,8 +55,10 @@ enum { GEMV_PLAIN = 0, GEMV_NORM = 1, GEMV_MERGE = 2 };
 // WAIT: the variant that is launched ahead of its inputs (GemvArgs::wait_done); a kernel of its own, so that the
 // ordinary one carries none of that code and the two show up separately in a kernel trace (the waiting one's
 // duration includes its wait).
-template <int NB, int RB, int ITERS, bool SWIGLU, int MODE, bool W8, bool WAIT>
-__global__ __launch_bounds__(512) void k_gemv(GemvArgs a)
+// BUF: passes whose weights are in flight at once (2: at least two passes, see gemv_go).  OCC: waves a SIMD that the registers
+// have to allow (4: two workgroups a CU).
+template <int NB, int RB, int ITERS, bool SWIGLU, int MODE, bool W8, bool WAIT, int BUF = 1, int OCC = 1>
+__global__ __launch_bounds__(512, OCC) void k_gemv(GemvArgs a)
 {
     constexpr int NW = SWIGLU ? 2 : 1;
     constexpr int WB = W8 ? 1 : 2;                       // bytes per weight
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(512) void k_gemv(GemvArgs a)
         kok[it] = kk[it] < K;
     }
 
-    WV wv[ITERS][NW][RB];
+    WV wq[BUF][ITERS][NW][RB];
     const char *Wb = static_cast<const char *>(a.W), *W2b = static_cast<const char *>(a.W2);
     auto ldw = [](const char *p) {
         if constexpr (W8) return ld8(p);
@@ -87,7 +89,7 @@ __global__ __launch_bounds__(512) void k_gemv(GemvArgs a)
     // int8: the thread that will store output (row r, batch entry b) of a pass fetches that row's scale
     // together with the pass's weights
     const int my_r = lg / NB;
-    float sc[NW] = {};
+    float sq[BUF][NW] = {};
     // Where the activations are requested ahead of the weights (the ordinary kernel with the fused normalisation),
     // every load of a pass is issued unconditionally, in straight-line code: a row past the group's range re-reads
     // the group's last row (a cache hit; its result is never stored) and a thread past the end of a short row reads
@@ -95,7 +97,7 @@ __global__ __launch_bounds__(512) void k_gemv(GemvArgs a)
     // counters are conservative across such blocks: it would wait for the weights before any arithmetic on the
     // activations that were requested ahead of them.
     constexpr bool ahead = MODE == GEMV_NORM && !WAIT;     // activations are requested ahead of the weights
-    auto load_rows = [&](int r0) {
+    auto load_rows = [&](WV (&wv)[ITERS][NW][RB], int r0) {
         if constexpr (!ahead) {
 #pragma unroll
             for (int it = 0; it < ITERS; ++it)
@@ -124,7 +126,7 @@ __global__ __launch_bounds__(512) void k_gemv(GemvArgs a)
             }
         }
     };
-    auto load_scales = [&](int r0) {
+    auto load_scales = [&](float (&sc)[NW], int r0) {
         if (W8 && lg < RB * NB && r0 + my_r < row_end) {
             sc[0] = a.scale[r0 + my_r];
             if (SWIGLU) sc[NW - 1] = a.scale2[r0 + my_r];
@@ -179,8 +181,11 @@ __global__ __launch_bounds__(512) void k_gemv(GemvArgs a)
     };
 
     int r0 = row_begin;
-    load_rows(r0);
-    load_scales(r0);
+#pragma unroll
+    for (int u = 0; u < BUF; ++u) {
+        load_rows(wq[u], r0 + u * RB);
+        load_scales(sq[u], r0 + u * RB);
+    }
 
     // ---- launched ahead of its inputs: the weights above travel (and then sit in registers) while the
     //      communication window is still running; one wave of the workgroup polls for the window's end
@@ -333,7 +338,7 @@ __global__ __launch_bounds__(512) void k_gemv(GemvArgs a)
     }
 
     // ---- stream the rows.  `passes` is the same for every group of the launch, so the barriers match.
-    for (int pass = 0; pass < a.passes; ++pass) {
+    auto step = [&](int pass, WV (&wv)[ITERS][NW][RB], float (&sc)[NW]) {
         float acc[NW][RB][NB];
 #pragma unroll
         for (int q = 0; q < NW; ++q)
@@ -358,9 +363,9 @@ __global__ __launch_bounds__(512) void k_gemv(GemvArgs a)
         float sc_now[NW];
 #pragma unroll
         for (int q = 0; q < NW; ++q) sc_now[q] = sc[q];
-        if (pass + 1 < a.passes) {   // next pass's loads fly during the reduction below
-            load_rows(r0);
-            load_scales(r0);
+        if (pass + BUF < a.passes) {   // a later pass's loads fly during the reduction below
+            load_rows(wv, r0 + (BUF - 1) * RB);
+            load_scales(sc, r0 + (BUF - 1) * RB);
         }
 
         if (wpg == 1) {
@@ -405,6 +410,11 @@ __global__ __launch_bounds__(512) void k_gemv(GemvArgs a)
             }
             __syncthreads();
         }
+    };
+    for (int pass = 0; pass < a.passes; pass += BUF) {
+#pragma unroll
+        for (int u = 0; u < BUF; ++u)
+            if (pass + u < a.passes) step(pass + u, wq[u], sq[u]);
     }
     (void)gw;
 }
@@ -424,7 +434,7 @@ struct GemvGeom {
     int gs_log2, groups, max_rows;
     long long blocks;
 };
-static GemvGeom gemv_geom(int N, int K, int iters, int threads, int rb)
+static GemvGeom gemv_geom(int N, int K, int iters, int threads, int rb, int most_blocks = 1024)
 {
     GemvGeom g;
     g.gs_log2 = 6;
@@ -435,7 +445,7 @@ static GemvGeom gemv_geom(int N, int K, int iters, int threads, int rb)
     const long long want = ((long long)N + (long long)rb * g.groups - 1) / ((long long)rb * g.groups);
     g.blocks = (want + 255) / 256 * 256;
     if (g.blocks < 256) g.blocks = 256;
-    if (g.blocks > 1024) g.blocks = 1024;
+    if (g.blocks > most_blocks) g.blocks = most_blocks;
     const long long slots = g.blocks * g.groups;
     g.max_rows = (int)((N + slots - 1) / slots);
     return g;
@@ -455,6 +465,24 @@ static hipError_t gemv_go(GemvArgs a, hipStream_t s)
             return hipGetLastError();
         } else {
             return hipErrorInvalidValue;     // only the kernels that open a block (fused add + norm) are launched ahead
+        }
+    }
+    // Gate | up in the ordinary launch: every workgroup repeats the normalisation (72 KB read per batch row at 4096 elements, its
+    // latency, a reduction), so up to 1024 of them a few rows each pay for it two to four times a CU, and while they do, only their
+    // first rows are on the way.  As many workgroups as are resident together, and the weights of two passes requested before the
+    // normalisation: rows of 4096 elements two workgroups a CU (58.7 MB, batch 2 15.8 -> 14.4 us, batch 1 13.0 -> 12.3), longer ones
+    // one (117 MB 25.9 -> 23.3, 235 MB 49.1 -> 42.0).  int8 has half the bytes in a row's request and gains nothing from the second
+    // pass (29 MB at batch 2 11.7 / 11.9); rows longer than 4096 take one workgroup a CU all the same (59 MB 19.0 -> 18.3, 117 MB
+    // 34.0 -> 32.3).  A matrix of a single pass keeps the spread.
+    if constexpr (SW && MODE == GEMV_NORM) {
+        constexpr int BUF = W8 ? 1 : 2, OCC = ITERS == 1 ? 4 : 2;
+        if constexpr (RB * BUF == 8 && (ITERS == 2 ? NB == 1 : !W8)) {
+            const GemvGeom g2 = gemv_geom(a.N, a.K, ITERS, threads, 8, ITERS == 1 ? 512 : 256);
+            if (g2.max_rows > RB) {
+                a.passes = (g2.max_rows + RB - 1) / RB;
+                PSV_LAUNCH((k_gemv<NB, RB, ITERS, SW, MODE, W8, false, BUF, OCC>), dim3((unsigned)g2.blocks), dim3(threads), 0, s, a);
+                return hipGetLastError();
+            }
         }
     }
     PSV_LAUNCH((k_gemv<NB, RB, ITERS, SW, MODE, W8, false>), dim3((unsigned)g.blocks), dim3(threads), 0, s, a);
