@@ -191,8 +191,8 @@ __global__ __launch_bounds__(64) void k_attn_prep(AttnPrepArgs a)
 #pragma unroll
         for (int e = 0; e < V; ++e) lo[ks].e[e] = hi[ks].e[e] = 0.f;
         if (ks < a.splits) {
-            lo[ks].v = *reinterpret_cast<const Vec *>(a.part + ks * stride + at);
-            hi[ks].v = *reinterpret_cast<const Vec *>(a.part + ks * stride + at + 64);
+            lo[ks].v = ld_once(reinterpret_cast<const Vec *>(a.part + ks * stride + at));
+            hi[ks].v = ld_once(reinterpret_cast<const Vec *>(a.part + ks * stride + at + 64));
         }
     }
     float2 cs[V];
@@ -1053,7 +1053,7 @@ __global__ __launch_bounds__(W * 64) void k_attn_merge(AttnArgs a)
     const size_t slot0 = ((size_t)b * nkv + kvh) * most, stride = (size_t)G * 128;       // chunk to chunk
     const float *po = a.part_o + (slot0 * G + g) * 128 + 2 * lane;
     auto pair_of = [&](int sp) { return *reinterpret_cast<const float2 *>(a.part_ml + ((slot0 + sp) * 16 + g) * 2); };
-    auto piece = [&](int sp, int n) { return *reinterpret_cast<const float2 *>(po + (size_t)min(sp, n - 1) * stride); };     // n >= 1
+    auto piece = [&](int sp, int n) { return ld_once(reinterpret_cast<const float2 *>(po + (size_t)min(sp, n - 1) * stride)); };     // n >= 1
     const int nc = PLAN ? a.plan.chunks[b] : a.n_chunks;
     constexpr int MU = kAttnMaxChunks / 64;
     float2 ml[MU];

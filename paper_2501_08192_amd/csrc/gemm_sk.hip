@@ -52,7 +52,7 @@ __global__ __launch_bounds__(128) void k_resid_sum(const float *__restrict__ res
             float4 t[GR];
 #pragma unroll
             for (int ks = 0; ks < GR; ++ks)
-                t[ks] = k0 + ks < delta_splits ? *reinterpret_cast<const float4 *>(d + (k0 + ks) * delta_stride)
+                t[ks] = k0 + ks < delta_splits ? ld_once(reinterpret_cast<const float4 *>(d + (k0 + ks) * delta_stride))
                                                : make_float4(0.f, 0.f, 0.f, 0.f);
             if (k0 == 0) e = t[0];
 #pragma unroll
@@ -1147,8 +1147,8 @@ __global__ __launch_bounds__(256) void k_sk_reduce(const float *__restrict__ par
         float4 t[kSkMaxSplits], t2[kSkMaxSplits];
 #pragma unroll
         for (int ks = 0; ks < kSkMaxSplits; ++ks) {
-            t[ks] = ks < splits ? *reinterpret_cast<const float4 *>(p + ks * split_stride) : make_float4(0.f, 0.f, 0.f, 0.f);
-            t2[ks] = ks < splits ? *reinterpret_cast<const float4 *>(p + ks * split_stride + NO) : make_float4(0.f, 0.f, 0.f, 0.f);
+            t[ks] = ks < splits ? ld_once(reinterpret_cast<const float4 *>(p + ks * split_stride)) : make_float4(0.f, 0.f, 0.f, 0.f);
+            t2[ks] = ks < splits ? ld_once(reinterpret_cast<const float4 *>(p + ks * split_stride + NO)) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
         float4 v = t[0], u = t2[0];
 #pragma unroll
