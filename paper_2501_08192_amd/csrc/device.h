@@ -272,6 +272,12 @@ __device__ __forceinline__ float2 ld_once(const float2 *p)
     return make_float2(v[0], v[1]);
 }
 
+__device__ __forceinline__ uint4 ld16_once(const uint16_t *p)
+{
+    typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p)));
+}
+
 __device__ __forceinline__ uint2 ld8(const void *p) { return *reinterpret_cast<const uint2 *>(p); }
 
 // int8 code j (0..3) of a 32-bit word as a float

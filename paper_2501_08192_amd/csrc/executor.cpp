@@ -141,6 +141,9 @@ Mat mat_of(const psv_ctx *c, const psv_layer_weights &w, uint32_t op)
     default: break;
     }
     m.tiled = c->d.weight_layout == PSV_W_TILED;
+    uint64_t layer = 0;
+    for (uint32_t o : {PSV_OP_QKV, PSV_OP_O, PSV_OP_GATE, PSV_OP_UP, PSV_OP_DOWN}) layer += op_mem_size(c->d, o, 1, 1);
+    m.once = c->d.n_layers * layer > 256u << 20;
     return m;
 }
 

@@ -244,7 +244,7 @@ __device__ __forceinline__ uint32_t xor4(uint4 v) { return v.x ^ v.y ^ v.z ^ v.w
 // ranges are up to twice as long as a chip filled with two workgroups a CU would give it (gemm_sk_splits); gate | up keeps its
 // short ranges and the registers of its waiting form.  Distance of the QKV sums from 64 bits at 11 slabs a range: one sum 2.44e-7,
 // apart 1.73e-7 (eight slabs a range, one sum: 2.18e-7); a step takes as long either way.
-template <int NB, int HOLD, bool APART, bool TURN = false>
+template <int NB, int HOLD, bool APART, bool TURN = false, bool TILED = false>
 __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj)
 {
     constexpr bool WAIT = HOLD > 0;
@@ -271,14 +271,15 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
     // so every load instruction of a wave covers 1 KiB of contiguous memory and the workgroup walks one contiguous run.
     const uint16_t *wp[2];
     bool wok[2];
-    const size_t wstep = a.tiled ? 8192 : 64;       // elements from one slab to the next
-    const int whalf = a.tiled ? 512 : 32;           // ... from the first 32 elements of a slab to the second
+    const bool tiled = TILED || a.tiled;
+    const size_t wstep = tiled ? 8192 : 64;       // elements from one slab to the next
+    const int whalf = tiled ? 512 : 32;           // ... from the first 32 elements of a slab to the second
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
         const int r = row_base + mt * 16 + i;
         wok[mt] = r < a.N;
         const int rr = wok[mt] ? r : 0;
-        if (a.tiled) {
+        if (tiled) {
             const int tile = blockIdx.x, tsplit = a.split_row >> 7;
             const uint16_t *t = tile < tsplit ? a.W + (size_t)tile * 128 * K : a.W2 + (size_t)(tile - tsplit) * 128 * K;
             wp[mt] = t + ((w * 2 + mt) * 2 * 64 + lane) * 8;
@@ -295,12 +296,18 @@ __global__ __launch_bounds__(256, 2) void k_gemm_sk(GemmSkArgs a, PrefetchJob pj
             f.a1[mt] = wok[mt] ? ld16(wp[mt] + (size_t)s * wstep + whalf) : zero16();
         }
     };
+    // TILED: weights in the tiled layout, whole lines, read once: non-temporal, so that they leave the L2 first and the activations,
+    // which every row tile reads again, stay.  Four layers, microseconds: 70B-shaped TP=8, batch 8, no windows 288 -> 275, cache-only
+    // 433 -> 422, launched ahead 396 -> 393; batch 32 334 -> 320, 479 -> 467, 453 -> 451; TP=4 batch 16 434 -> 397, batch 64 with windows
+    // 766 -> 745.  Not for row-major weights, whose loads take half a line at a time and would fetch it twice (6 MB QKV at batch 5
+    // 5.8 -> 6.3 us), nor for a model that fits the memory-side cache (Mat::once).
+    auto ldw = [](const uint16_t *p) { if constexpr (TILED) return ld16_once(p); else return ld16(p); };
     auto load_w_all = [&](int s, WFrag &f) {   // unpredicated: a row past N reads row 0 (wp) and is never stored
         s = slab(s);
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) {
-            f.a0[mt] = ld16(wp[mt] + (size_t)s * wstep);
-            f.a1[mt] = ld16(wp[mt] + (size_t)s * wstep + whalf);
+            f.a0[mt] = ldw(wp[mt] + (size_t)s * wstep);
+            f.a1[mt] = ldw(wp[mt] + (size_t)s * wstep + whalf);
         }
     };
     // activation slab: NB*256 16-byte units, unit u = ((tile*2 + plane)*16 + row)*8 + segment.  A thread has the same plane, row
@@ -1113,22 +1120,25 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
         else PSV_LAUNCH((k_gemm_sk<2, 1, false>), grid, dim3(256), 0, s, a, pj);
         return hipGetLastError();
     }
-    switch (turn ? nb + 8 : W2.w ? nb : nb + 4) {        // one matrix: the planes' products summed apart
-    case 1: PSV_LAUNCH((k_gemm_sk<1, 0, false>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 2: PSV_LAUNCH((k_gemm_sk<2, 0, false>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 3: PSV_LAUNCH((k_gemm_sk<3, 0, false>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 4: PSV_LAUNCH((k_gemm_sk<4, 0, false>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 5: PSV_LAUNCH((k_gemm_sk<1, 0, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 6: PSV_LAUNCH((k_gemm_sk<2, 0, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 7: PSV_LAUNCH((k_gemm_sk<3, 0, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 8: PSV_LAUNCH((k_gemm_sk<4, 0, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 9: PSV_LAUNCH((k_gemm_sk<1, 0, false, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 10: PSV_LAUNCH((k_gemm_sk<2, 0, false, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 11: PSV_LAUNCH((k_gemm_sk<3, 0, false, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
-    case 12: PSV_LAUNCH((k_gemm_sk<4, 0, false, true>), grid, dim3(256), 0, s, a, PrefetchJob{}); break;
+    auto go = [&](auto kernel) {
+        PSV_LAUNCH(kernel, grid, dim3(256), 0, s, a, PrefetchJob{});
+        return hipGetLastError();
+    };
+    // one matrix: the planes' products summed apart
+    auto pick = [&](auto tiles, auto layout) {
+        constexpr int T = decltype(tiles)::value;
+        constexpr bool L = decltype(layout)::value;
+        return turn ? go(k_gemm_sk<T, 0, false, true, L>) : W2.w ? go(k_gemm_sk<T, 0, false, false, L>) : go(k_gemm_sk<T, 0, true, false, L>);
+    };
+    // tiled weights that are not in the memory-side cache from the step before: read non-temporally (k_gemm_sk, TILED)
+    auto by_layout = [&](auto tiles) { return W.tiled && W.once ? pick(tiles, std::true_type{}) : pick(tiles, std::false_type{}); };
+    switch (nb) {
+    case 1: return by_layout(std::integral_constant<int, 1>{});
+    case 2: return by_layout(std::integral_constant<int, 2>{});
+    case 3: return by_layout(std::integral_constant<int, 3>{});
+    case 4: return by_layout(std::integral_constant<int, 4>{});
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 // Gate | up: the N columns are summed over the splits (split order) and become silu(gate) * up, [batch][N/2], stored as fp32

@@ -38,6 +38,7 @@ struct GemvArgs {
     float *out_h;               // FUSE_NORM: normalised activations, written by workgroup 0 (may be null)
     float *out;                 // [NB][N]
     int N, K, gs_log2, passes;
+    int once;                   // bf16 weights: Mat::once
     // MODE_MERGE: the activations are the attention output, merged here from the split-K partials
     const float *part_ml, *part_o;
     int nkv, G, nc;             // kv heads, query heads per kv head, chunks per (sequence, kv head)
@@ -57,7 +58,7 @@ enum { GEMV_PLAIN = 0, GEMV_NORM = 1, GEMV_MERGE = 2 };
 // duration includes its wait).
 // BUF: passes whose weights are in flight at once (2: at least two passes, see gemv_go).  OCC: waves a SIMD that the registers
 // have to allow (4: two workgroups a CU).
-template <int NB, int RB, int ITERS, bool SWIGLU, int MODE, bool W8, bool WAIT, int BUF = 1, int OCC = 1>
+template <int NB, int RB, int ITERS, bool SWIGLU, int MODE, bool W8, bool WAIT, bool ONCE = false, int BUF = 1, int OCC = 1>
 __global__ __launch_bounds__(512, OCC) void k_gemv(GemvArgs a)
 {
     constexpr int NW = SWIGLU ? 2 : 1;
@@ -84,6 +85,7 @@ __global__ __launch_bounds__(512, OCC) void k_gemv(GemvArgs a)
     const char *Wb = static_cast<const char *>(a.W), *W2b = static_cast<const char *>(a.W2);
     auto ldw = [](const char *p) {
         if constexpr (W8) return ld8(p);
+        else if constexpr (ONCE) return ld16_once(reinterpret_cast<const uint16_t *>(p));
         else return *reinterpret_cast<const uint4 *>(p);
     };
     // int8: the thread that will store output (row r, batch entry b) of a pass fetches that row's scale
@@ -459,10 +461,18 @@ static hipError_t gemv_go(GemvArgs a, hipStream_t s)
     a.gs_log2 = g.gs_log2;
     a.passes = (g.max_rows + RB - 1) / RB;
     if (a.passes < 1) a.passes = 1;
+    // Weights that nothing of will be in the memory-side cache when they are needed again are read non-temporally (whole rows, once):
+    // they leave room in L2 for the activations that every workgroup reads.  8B-shaped TP=4 shard, batch 2 356 -> 344 us for 8 layers,
+    // 70B-shaped shards, batch 1, TP=4 386 -> 362 for 4, TP=8 with windows 753 -> 739 for 8.  A model that does fit loses by it (23 MB
+    // a layer, 8 layers, batch 2 227 -> 242), so the line is that cache's 256 MB.
+    auto go = [&](auto kernel, auto kernel_once, long long blocks) {
+        if (a.once) PSV_LAUNCH(kernel_once, dim3((unsigned)blocks), dim3(threads), 0, s, a);
+        else PSV_LAUNCH(kernel, dim3((unsigned)blocks), dim3(threads), 0, s, a);
+        return hipGetLastError();
+    };
     if (a.wait_done) {
         if constexpr (MODE == GEMV_NORM) {
-            PSV_LAUNCH((k_gemv<NB, RB, ITERS, SW, MODE, W8, true>), dim3((unsigned)g.blocks), dim3(threads), 0, s, a);
-            return hipGetLastError();
+            return go(k_gemv<NB, RB, ITERS, SW, MODE, W8, true, false>, k_gemv<NB, RB, ITERS, SW, MODE, W8, true, !W8>, g.blocks);
         } else {
             return hipErrorInvalidValue;     // only the kernels that open a block (fused add + norm) are launched ahead
         }
@@ -480,13 +490,11 @@ static hipError_t gemv_go(GemvArgs a, hipStream_t s)
             const GemvGeom g2 = gemv_geom(a.N, a.K, ITERS, threads, 8, ITERS == 1 ? 512 : 256);
             if (g2.max_rows > RB) {
                 a.passes = (g2.max_rows + RB - 1) / RB;
-                PSV_LAUNCH((k_gemv<NB, RB, ITERS, SW, MODE, W8, false, BUF, OCC>), dim3((unsigned)g2.blocks), dim3(threads), 0, s, a);
-                return hipGetLastError();
+                return go(k_gemv<NB, RB, ITERS, SW, MODE, W8, false, false, BUF, OCC>, k_gemv<NB, RB, ITERS, SW, MODE, W8, false, !W8, BUF, OCC>, g2.blocks);
             }
         }
     }
-    PSV_LAUNCH((k_gemv<NB, RB, ITERS, SW, MODE, W8, false>), dim3((unsigned)g.blocks), dim3(threads), 0, s, a);
-    return hipGetLastError();
+    return go(k_gemv<NB, RB, ITERS, SW, MODE, W8, false, false>, k_gemv<NB, RB, ITERS, SW, MODE, W8, false, !W8>, g.blocks);
 }
 
 // Rows per pass: as many as keep 128 bytes (x ITERS) of weight loads in flight per thread (8 rows of bf16, 16
@@ -534,7 +542,7 @@ static hipError_t gemv_dispatch(const GemvArgs &a, int batch, hipStream_t s)
 hipError_t launch_gemv(Mat W, Mat W2, const float *x, float *out, int batch, int N, int K, hipStream_t s)
 {
     GemvArgs a{};
-    a.W = W.w; a.W2 = W2.w; a.scale = W.scale; a.scale2 = W2.scale; a.x = x; a.out = out; a.N = N; a.K = K;
+    a.W = W.w; a.W2 = W2.w; a.once = W.once; a.scale = W.scale; a.scale2 = W2.scale; a.x = x; a.out = out; a.N = N; a.K = K;
     return gemv_dispatch<GEMV_PLAIN>(a, batch, s);
 }
 
@@ -547,7 +555,7 @@ hipError_t launch_gemv_norm(Mat W, Mat W2, const float *res, const float *delta,
         a.wait_done = wait->done; a.wait_seq = wait->seq; a.wait_iters = wait->iters; a.wait_ticks = wait->ticks;
         a.wait_err = wait->err;
     }
-    a.W = W.w; a.W2 = W2.w; a.scale = W.scale; a.scale2 = W2.scale; a.res = res; a.delta = delta; a.gain = gain; a.eps = eps; a.out_res = out_res; a.out_h = out_h;
+    a.W = W.w; a.W2 = W2.w; a.once = W.once; a.scale = W.scale; a.scale2 = W2.scale; a.res = res; a.delta = delta; a.gain = gain; a.eps = eps; a.out_res = out_res; a.out_h = out_h;
     a.out = out; a.N = N; a.K = K;
     return gemv_dispatch<GEMV_NORM>(a, batch, s);
 }
@@ -561,7 +569,7 @@ hipError_t launch_gemv_merge(Mat W, const float *part_ml, const float *part_o, i
                              int n_chunks, float *out_attn, float *out, int batch, int N, hipStream_t s)
 {
     GemvArgs a{};
-    a.W = W.w; a.scale = W.scale; a.part_ml = part_ml; a.part_o = part_o; a.nkv = nkv; a.G = nq / nkv; a.nc = n_chunks; a.out_h = out_attn;
+    a.W = W.w; a.once = W.once; a.scale = W.scale; a.part_ml = part_ml; a.part_o = part_o; a.nkv = nkv; a.G = nq / nkv; a.nc = n_chunks; a.out_h = out_attn;
     a.out = out; a.N = N; a.K = nq * 128;
     return gemv_dispatch<GEMV_MERGE>(a, batch, s);
 }

@@ -62,6 +62,7 @@ struct Mat {
     const void *w = nullptr;
     const float *scale = nullptr;
     bool tiled = false;          // PSV_W_TILED storage (matrix-core projections only)
+    bool once = false;           // the model's weights do not fit the memory-side cache: nothing of them is there in the next step
 };
 
 // ---- kernel launchers ---------------------------------------------------------------------
