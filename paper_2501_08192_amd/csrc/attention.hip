@@ -339,9 +339,12 @@ __device__ __forceinline__ AttnChunk attn_chunk(const AttnArgs &a, int kvh)
 //  * main loop: all G heads ride in the N side of the MFMAs, so K and V are read from HBM once.
 //        S^T[token][g]  = K[token][:] . Q[g][:]          A = K rows (token-major in the pool)
 //        O^T[chan][g]  += V^T[chan][token] P[g][token]   A = V^T rows (channel-major in the pool)
-//    Tile 1 of a 32-token group covers tokens {8q+0..3}, tile 2 tokens {8q+4..7} (q = 0..3), so after
-//    the two S^T MFMAs lane (g, q) holds the scores of the 8 consecutive tokens 8q..8q+7 of its head:
-//    exactly the B-fragment the O^T MFMA needs.  Probabilities never leave registers.
+//    A load instruction of K takes whole 128-byte lines, 8 tokens x 64 channels: row i of the A operand is half a line, the two
+//    halves of a token in neighbouring rows.  Each half needs its own channels of Q, so every operand is multiplied with both
+//    and a lane adds the two useful rows: twice the score products, on matrix cores that idle.  What that buys is the
+//    non-temporal load (ONCE), which reads scattered 4 KB blocks at 6.5 TB/s instead of 5.75 (and at 5.1 when an instruction
+//    takes half lines): 537 MB 103.8 -> 87.9 us, 268 MB 56.7 -> 49.3, 134 MB 29.4 -> 25.8.  The four groups of 8 tokens are chosen so that lane (g, q) ends up with the scores of the 8 consecutive tokens
+//    8q..8q+7 of its head: exactly the B-fragment the O^T MFMA needs.  Probabilities never leave registers.
 //  * epilogue: the 4 waves merge through LDS and the workgroup stores one partial (max, sum, O);
 //    k_attn_merge then combines the partials of a (sequence, kv head) in chunk order.
 //
@@ -351,7 +354,7 @@ __device__ __forceinline__ AttnChunk attn_chunk(const AttnArgs &a, int kvh)
 // needs, per lane, eight consecutive tokens of one channel: each wave passes its 32 x 128 tile through LDS (whole
 // 256-byte token rows in, 16-byte pieces XOR-swizzled by the token's group of eight so that the transposed 2-byte
 // reads of all 64 lanes fall into different banks) and picks its fragments up transposed.
-template <bool TM, bool PREP>
+template <bool TM, bool PREP, bool ONCE>
 __global__ __launch_bounds__(256, PREP ? 2 : 1) void k_attn(AttnArgs a)
 {
     __shared__ __align__(16) uint16_t fresh[2][128];      // the new key and value row
@@ -373,29 +376,30 @@ __global__ __launch_bounds__(256, PREP ? 2 : 1) void k_attn(AttnArgs a)
     // ---- K/V tile loader.  The addresses depend on the page table only, not on the sequence length (tokens
     //      past the span are masked later, and every logical block below max_blocks maps into the pool), so
     //      each wave issues the loads of its first tile right away, ahead of everything else in the kernel.
-    const int tau1 = 8 * (i >> 2) + (i & 3);          // token (within the 32-token group) of K row i, tile 1
-    uint4 ka[4], kb[4], vf[8];
+    // K row i of load (j, line): token 8 * (i / 4) + 2j + (i / 2) % 2 of the 32, half i % 2 of a 128-byte line
+    const int tau = 8 * (i >> 2) + ((i >> 1) & 1), half = (i & 1) * 32 + q4 * 8;
+    auto ld = [](const uint16_t *p) { if constexpr (ONCE) return ld16_once(p); else return ld16(p); };
+    uint4 kf[4][2], vf[8];
     auto lookup = [&](int t0, int &blkA, int &blkB) {
         const int lb = t0 >> 4;
         blkA = kv_phys_block(kv.page_table, kv.max_blocks, kv.num_pool_blocks, b, lb);
         blkB = (lb + 1 < kv.max_blocks) ? kv_phys_block(kv.page_table, kv.max_blocks, kv.num_pool_blocks, b, lb + 1) : -1;
     };
     auto load_blocks = [&](int blkA, int blkB) {
-        // K fragments: tile 1 row i = token tau1, tile 2 row i = token tau1 + 4
         {
             const int blk = (i < 8) ? blkA : blkB;
             if (blk >= 0) {
-                const uint16_t *base = TM ? kv.k_pool + (((size_t)blk * 16 + (tau1 & 15)) * nkv + kvh) * 128 + q4 * 8
-                                          : kv.k_pool + (((size_t)blk * nkv + kvh) * 16 + (tau1 & 15)) * 128 + q4 * 8;
-                const size_t row4 = TM ? (size_t)4 * nkv * 128 : (size_t)4 * 128;      // four tokens further
+                const uint16_t *base = TM ? kv.k_pool + (((size_t)blk * 16 + (tau & 15)) * nkv + kvh) * 128 + half
+                                          : kv.k_pool + (((size_t)blk * nkv + kvh) * 16 + (tau & 15)) * 128 + half;
+                const size_t row2 = TM ? (size_t)2 * nkv * 128 : (size_t)2 * 128;      // two tokens further
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    ka[ks] = ld16(base + ks * 32);
-                    kb[ks] = ld16(base + row4 + ks * 32);
+                for (int j = 0; j < 4; ++j) {
+                    kf[j][0] = ld(base + j * row2);
+                    kf[j][1] = ld(base + j * row2 + 64);
                 }
             } else {
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) { ka[ks] = zero16(); kb[ks] = zero16(); }
+                for (int j = 0; j < 4; ++j) { kf[j][0] = zero16(); kf[j][1] = zero16(); }
             }
         }
         if constexpr (TM) {
@@ -403,7 +407,7 @@ __global__ __launch_bounds__(256, PREP ? 2 : 1) void k_attn(AttnArgs a)
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const int blk = j < 4 ? blkA : blkB;
-                vf[j] = blk >= 0 ? ld16(kv.v_pool + (((size_t)blk * 16 + ((4 * j + q4) & 15)) * nkv + kvh) * 128 + i * 8) : zero16();
+                vf[j] = blk >= 0 ? ld(kv.v_pool + (((size_t)blk * 16 + ((4 * j + q4) & 15)) * nkv + kvh) * 128 + i * 8) : zero16();
             }
             return;
         }
@@ -413,7 +417,7 @@ __global__ __launch_bounds__(256, PREP ? 2 : 1) void k_attn(AttnArgs a)
             if (blk >= 0) {
                 const uint16_t *base = kv.v_pool + (((size_t)blk * nkv + kvh) * 128 + i) * 16 + (q4 & 1) * 8;
 #pragma unroll
-                for (int dg = 0; dg < 8; ++dg) vf[dg] = ld16(base + dg * 16 * 16);
+                for (int dg = 0; dg < 8; ++dg) vf[dg] = ld(base + dg * 16 * 16);
             } else {
 #pragma unroll
                 for (int dg = 0; dg < 8; ++dg) vf[dg] = zero16();
@@ -553,10 +557,11 @@ __global__ __launch_bounds__(256, PREP ? 2 : 1) void k_attn(AttnArgs a)
         if (blk >= 0 && early && pos >= t_first && pos < t_first + kAttnTileTokens) {
             const int dt = pos - t_first;
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const uint4 k8 = *reinterpret_cast<const uint4 *>(&fresh[0][ks * 32 + q4 * 8]);
-                if (tau1 == dt) ka[ks] = k8;
-                if (tau1 + 4 == dt) kb[ks] = k8;
+            for (int c = 0; c < 2; ++c) {
+                const uint4 k8 = *reinterpret_cast<const uint4 *>(&fresh[0][c * 64 + half]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (tau + 2 * j == dt) kf[j][c] = k8;
             }
             if constexpr (TM) {
                 const uint4 v8 = *reinterpret_cast<const uint4 *>(&fresh[1][i * 8]);
@@ -587,21 +592,26 @@ __global__ __launch_bounds__(256, PREP ? 2 : 1) void k_attn(AttnArgs a)
     for (int t0 = t_first; t0 < t_end; t0 += kAttnWaves * kAttnTileTokens) {
         if (t0 != t_first || !early) load_tile(t0);
 
-        f32x4 s1 = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};
+        // d[j][h]: rows of half h hold the products of their line halves with the query's channels 64c + 32h; the other rows nothing of use
+        f32x4 d[4][2];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[ks]), qfl[ks], s1, 0, 0, 0);
-            s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kb[ks]), qfl[ks], s2, 0, 0, 0);
-            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[ks]), qf[ks], s1, 0, 0, 0);
-            s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kb[ks]), qf[ks], s2, 0, 0, 0);
-        }
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < 2; ++c) x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[j][c]), qfl[2 * c + h], x, 0, 0, 0);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[j][c]), qf[2 * c + h], x, 0, 0, 0);
+                d[j][h] = x;
+            }
         // lane (g = i, q4) now holds tokens t0 + 8*q4 + e, e = 0..7
         float sv[8];
         const int tl = t0 + 8 * q4;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sv[e] = (tl + e < t_end) ? s1[e] * kScale : -INFINITY;
-            sv[e + 4] = (tl + e + 4 < t_end) ? s2[e] * kScale : -INFINITY;
+        for (int e = 0; e < 8; ++e) {
+            const int j = e >> 1, r = 2 * (e & 1);
+            sv[e] = (tl + e < t_end) ? (d[j][0][r] + d[j][1][r + 1]) * kScale : -INFINITY;
         }
         float tmax = sv[0];
 #pragma unroll
@@ -1140,8 +1150,10 @@ template <bool PREP>
 static void launch_attn_kernel(const AttnArgs &a, dim3 grid, hipStream_t s)
 {
     if (a.kv.int8) PSV_LAUNCH((k_attn_q8<PREP>), grid, dim3(256), 0, s, a);
-    else if (a.kv.token_major) PSV_LAUNCH((k_attn<true, PREP>), grid, dim3(256), 0, s, a);
-    else PSV_LAUNCH((k_attn<false, PREP>), grid, dim3(256), 0, s, a);
+    else if (a.kv.token_major && a.kv.once) PSV_LAUNCH((k_attn<true, PREP, true>), grid, dim3(256), 0, s, a);
+    else if (a.kv.token_major) PSV_LAUNCH((k_attn<true, PREP, false>), grid, dim3(256), 0, s, a);
+    else if (a.kv.once) PSV_LAUNCH((k_attn<false, PREP, true>), grid, dim3(256), 0, s, a);
+    else PSV_LAUNCH((k_attn<false, PREP, false>), grid, dim3(256), 0, s, a);
 }
 
 hipError_t launch_attn(const float *qkv, const float2 *rope, KvView kv, int batch, int nq, int nkv, AttnSplit sp,

@@ -74,6 +74,14 @@ Workspace layout_workspace(const psv_model_desc &d)
     return w;
 }
 
+// Bytes a step reads at most, against the memory-side cache's 256 MB: what exceeds it is not there any more in the next step.
+static bool read_once(const psv_model_desc &d, bool with_cache)
+{
+    uint64_t layer = with_cache ? op_mem_size(d, PSV_OP_ATTN, d.max_batch, d.max_seq) : 0;
+    for (uint32_t o : {PSV_OP_QKV, PSV_OP_O, PSV_OP_GATE, PSV_OP_UP, PSV_OP_DOWN}) layer += op_mem_size(d, o, 1, 1);
+    return d.n_layers * layer > 256u << 20;
+}
+
 KvView kv_view(const psv_ctx *c, uint32_t layer)
 {
     KvView v;
@@ -81,6 +89,7 @@ KvView kv_view(const psv_ctx *c, uint32_t layer)
     v.v_pool = static_cast<uint16_t *>(c->v_pools[layer]);
     v.int8 = c->d.kv_format == PSV_FMT_INT8 ? 1 : 0;
     v.token_major = c->d.kv_layout == PSV_KV_TOKEN_MAJOR ? 1 : 0;
+    v.once = read_once(c->d, true) ? 1 : 0;
     v.page_table = c->kv.page_table;
     v.max_blocks = (int)c->kv.max_blocks;
     {
@@ -141,9 +150,7 @@ Mat mat_of(const psv_ctx *c, const psv_layer_weights &w, uint32_t op)
     default: break;
     }
     m.tiled = c->d.weight_layout == PSV_W_TILED;
-    uint64_t layer = 0;
-    for (uint32_t o : {PSV_OP_QKV, PSV_OP_O, PSV_OP_GATE, PSV_OP_UP, PSV_OP_DOWN}) layer += op_mem_size(c->d, o, 1, 1);
-    m.once = c->d.n_layers * layer > 256u << 20;
+    m.once = read_once(c->d, false);
     return m;
 }
 

@@ -43,6 +43,7 @@ struct KvView {
     uint16_t *v_pool;
     int int8;
     int token_major;             // bf16 pools laid out [block][16 tokens][kv head][128] (both K and V)
+    int once;                    // weights and the largest cache together exceed the memory-side cache (Mat::once)
     const int32_t *page_table;   // null => contiguous
     int max_blocks;
     int max_tokens;              // longest valid sequence: min(max_blocks * 16, the descriptor's max_seq); the
