@@ -278,6 +278,11 @@ __device__ __forceinline__ uint4 ld16_once(const uint16_t *p)
     return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p)));
 }
 
+__device__ __forceinline__ uint2 ld8_once(const void *p)
+{
+    typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint2, __builtin_nontemporal_load(reinterpret_cast<const u32x2_t *>(p)));
+}
 __device__ __forceinline__ uint2 ld8(const void *p) { return *reinterpret_cast<const uint2 *>(p); }
 
 // int8 code j (0..3) of a 32-bit word as a float

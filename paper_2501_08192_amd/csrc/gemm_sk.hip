@@ -617,7 +617,11 @@ constexpr int kSkI8Blocks = 18;    // most 128-element blocks of a waiting workg
 // HOLD, pj: as for k_gemm_sk.  The waiting variant keeps the 4 blocks of its register ring, or those and 2 more in LDS
 // (16 KiB each), on chip.  The operand's block scales share cache lines between producer workgroups of different XCDs,
 // so the waiting variant reads those of its K range with device-coherent loads, once, after the wait.
-template <int NB, int HOLD>
+// TILED: as for k_gemm_sk, where the weights do not stay in the memory-side cache.  Four layers, no windows / cache-only, microseconds: 70B-shaped
+// TP=8, batch 8 241 -> 221 / 379 -> 371, batch 32 272 -> 262 / 417 -> 413; TP=4 batch 16 301 -> 286 / 448 -> 440, batch 64 467 -> 450 / 606 -> 604.  One batch tile
+// keeps the ordinary loads where windows prefetch: out of the memory-side cache they are the faster ones (batch 8 launched into its
+// windows, eight layers 732 / 744).
+template <int NB, int HOLD, bool TILED = false>
 __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob pj)
 {
     constexpr bool WAIT = HOLD > 0;
@@ -637,14 +641,15 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void k_gemm_sk_i8(GemmI8Args 
 
     const int8_t *wp[2];
     bool wok[2];
-    const size_t wstep = a.tiled ? 16384 : 128;     // bytes from one block to the next
-    const int wslab = a.tiled ? 8192 : 64;          // ... from its first slab to its second
+    const bool tiled = TILED || a.tiled;
+    const size_t wstep = tiled ? 16384 : 128;     // bytes from one block to the next
+    const int wslab = tiled ? 8192 : 64;          // ... from its first slab to its second
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
         const int r = row_base + mt * 16 + i;
         wok[mt] = r < a.N;
         const int rr = wok[mt] ? r : 0;
-        if (a.tiled) {
+        if (tiled) {
             const int tile = blockIdx.x, tsplit = a.split_row >> 7;
             const int8_t *t = tile < tsplit ? a.W + (size_t)tile * 128 * K : a.W2 + (size_t)(tile - tsplit) * 128 * K;
             wp[mt] = t + ((w * 2 + mt) * 64 + lane) * 16;
@@ -658,7 +663,11 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void k_gemm_sk_i8(GemmI8Args 
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) f.c[h][mt] = ld16(reinterpret_cast<const uint16_t *>(wp[mt] + (size_t)k * wstep + h * wslab));
+            for (int h = 0; h < 2; ++h) {
+                const uint16_t *p = reinterpret_cast<const uint16_t *>(wp[mt] + (size_t)k * wstep + h * wslab);
+                if constexpr (TILED) f.c[h][mt] = ld16_once(p);
+                else f.c[h][mt] = ld16(p);
+            }
     };
     // activation block: NB*256 16-byte units, unit u = ((tile*2 + digit)*16 + row)*8 + segment: a thread has the same digit, row and
     // segment of every tile, one 32-bit offset from uniform bases serves all its loads (see k_gemm_sk)
@@ -1089,14 +1098,18 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
             else PSV_LAUNCH((k_gemm_sk_i8<1, 1>), grid, dim3(256), 0, s, q, pj);
             return hipGetLastError();
         }
+        auto go8 = [&](auto kernel, auto kernel_once) {
+            if (W.tiled && W.once && !(nb == 1 && W.warm)) PSV_LAUNCH(kernel_once, grid, dim3(256), 0, s, q, PrefetchJob{});
+            else PSV_LAUNCH(kernel, grid, dim3(256), 0, s, q, PrefetchJob{});
+            return hipGetLastError();
+        };
         switch (nb) {
-        case 1: PSV_LAUNCH((k_gemm_sk_i8<1, 0>), grid, dim3(256), 0, s, q, PrefetchJob{}); break;
-        case 2: PSV_LAUNCH((k_gemm_sk_i8<2, 0>), grid, dim3(256), 0, s, q, PrefetchJob{}); break;
-        case 3: PSV_LAUNCH((k_gemm_sk_i8<3, 0>), grid, dim3(256), 0, s, q, PrefetchJob{}); break;
-        case 4: PSV_LAUNCH((k_gemm_sk_i8<4, 0>), grid, dim3(256), 0, s, q, PrefetchJob{}); break;
+        case 1: return go8(k_gemm_sk_i8<1, 0>, k_gemm_sk_i8<1, 0, true>);
+        case 2: return go8(k_gemm_sk_i8<2, 0>, k_gemm_sk_i8<2, 0, true>);
+        case 3: return go8(k_gemm_sk_i8<3, 0>, k_gemm_sk_i8<3, 0, true>);
+        case 4: return go8(k_gemm_sk_i8<4, 0>, k_gemm_sk_i8<4, 0, true>);
         default: return hipErrorInvalidValue;
         }
-        return hipGetLastError();
     }
     GemmSkArgs a{};
     a.ssq = ssq; a.eps = eps;

@@ -38,7 +38,7 @@ struct GemvArgs {
     float *out_h;               // FUSE_NORM: normalised activations, written by workgroup 0 (may be null)
     float *out;                 // [NB][N]
     int N, K, gs_log2, passes;
-    int once;                   // bf16 weights: Mat::once
+    int once;                   // Mat::once
     // MODE_MERGE: the activations are the attention output, merged here from the split-K partials
     const float *part_ml, *part_o;
     int nkv, G, nc;             // kv heads, query heads per kv head, chunks per (sequence, kv head)
@@ -84,7 +84,8 @@ __global__ __launch_bounds__(512, OCC) void k_gemv(GemvArgs a)
     WV wq[BUF][ITERS][NW][RB];
     const char *Wb = static_cast<const char *>(a.W), *W2b = static_cast<const char *>(a.W2);
     auto ldw = [](const char *p) {
-        if constexpr (W8) return ld8(p);
+        if constexpr (W8 && ONCE) return ld8_once(p);
+        else if constexpr (W8) return ld8(p);
         else if constexpr (ONCE) return ld16_once(reinterpret_cast<const uint16_t *>(p));
         else return *reinterpret_cast<const uint4 *>(p);
     };
@@ -463,7 +464,7 @@ static hipError_t gemv_go(GemvArgs a, hipStream_t s)
     if (a.passes < 1) a.passes = 1;
     // Weights that nothing of will be in the memory-side cache when they are needed again are read non-temporally (whole rows, once):
     // they leave room in L2 for the activations that every workgroup reads.  8B-shaped TP=4 shard, batch 2 356 -> 344 us for 8 layers,
-    // 70B-shaped shards, batch 1, TP=4 386 -> 362 for 4, TP=8 with windows 753 -> 739 for 8.  A model that does fit loses by it (23 MB
+    // 70B-shaped shards, batch 1, TP=4 386 -> 362 for 4 (int8 279 -> 264), TP=8 with windows 753 -> 739 for 8.  A model that does fit loses by it (23 MB
     // a layer, 8 layers, batch 2 227 -> 242), so the line is that cache's 256 MB.
     auto go = [&](auto kernel, auto kernel_once, long long blocks) {
         if (a.once) PSV_LAUNCH(kernel_once, dim3((unsigned)blocks), dim3(threads), 0, s, a);
@@ -472,7 +473,7 @@ static hipError_t gemv_go(GemvArgs a, hipStream_t s)
     };
     if (a.wait_done) {
         if constexpr (MODE == GEMV_NORM) {
-            return go(k_gemv<NB, RB, ITERS, SW, MODE, W8, true, false>, k_gemv<NB, RB, ITERS, SW, MODE, W8, true, !W8>, g.blocks);
+            return go(k_gemv<NB, RB, ITERS, SW, MODE, W8, true, false>, k_gemv<NB, RB, ITERS, SW, MODE, W8, true, true>, g.blocks);
         } else {
             return hipErrorInvalidValue;     // only the kernels that open a block (fused add + norm) are launched ahead
         }
@@ -490,11 +491,11 @@ static hipError_t gemv_go(GemvArgs a, hipStream_t s)
             const GemvGeom g2 = gemv_geom(a.N, a.K, ITERS, threads, 8, ITERS == 1 ? 512 : 256);
             if (g2.max_rows > RB) {
                 a.passes = (g2.max_rows + RB - 1) / RB;
-                return go(k_gemv<NB, RB, ITERS, SW, MODE, W8, false, false, BUF, OCC>, k_gemv<NB, RB, ITERS, SW, MODE, W8, false, !W8, BUF, OCC>, g2.blocks);
+                return go(k_gemv<NB, RB, ITERS, SW, MODE, W8, false, false, BUF, OCC>, k_gemv<NB, RB, ITERS, SW, MODE, W8, false, true, BUF, OCC>, g2.blocks);
             }
         }
     }
-    return go(k_gemv<NB, RB, ITERS, SW, MODE, W8, false, false>, k_gemv<NB, RB, ITERS, SW, MODE, W8, false, !W8>, g.blocks);
+    return go(k_gemv<NB, RB, ITERS, SW, MODE, W8, false, false>, k_gemv<NB, RB, ITERS, SW, MODE, W8, false, true>, g.blocks);
 }
 
 // Rows per pass: as many as keep 128 bytes (x ITERS) of weight loads in flight per thread (8 rows of bf16, 16

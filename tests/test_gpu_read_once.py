@@ -1,5 +1,5 @@
 """A model that exceeds the memory-side cache is read with other load instructions (non-temporal) than one that fits; nothing else differs.
-The same layer as the only one of its model and as the first of forty (the others are described but not materialised): the same
+The same layer as the only one of its model and as the first of eighty (the others are described but not materialised): the same
 bits, on the vector path, with one to four batch tiles, for every layout, and launched into a window."""
 import pytest
 import torch
@@ -14,10 +14,11 @@ pytestmark = pytest.mark.gpu
     (1, "bf16", "bf16", "row", "head", True), (2, "bf16", "bf16", "row", "token", False), (1, "int8", "int8", "row", "head", True),
     (3, "bf16", "bf16", "tiled", "head", True), (17, "bf16", "bf16", "tiled", "token", True), (33, "bf16", "int8", "tiled", "head", False),
     (64, "bf16", "bf16", "tiled", "head", True), (16, "bf16", "bf16", "row", "head", False), (40, "int8", "int8", "tiled", "head", True),
+    (3, "int8", "bf16", "tiled", "head", False), (17, "int8", "int8", "tiled", "head", True), (64, "int8", "bf16", "tiled", "head", True),
 ])
 def test_same_bits_as_the_only_layer_and_as_the_first_of_many(batch, weights, kv, layout, kv_layout, paged):
     outs = []
-    for n_layers in (1, 40):           # 10 MB a layer (int8 5 MB with 40 layers still fits, by its weights alone)
+    for n_layers in (1, 80):           # 11.5 MB a layer in bf16, 5.8 MB in int8
         w = synth.Workload("once", n_layers, 1024, 8, 2, 128, 1024, batch, 700, paged, (8.0, 8.0), weight_format=weights, kv_format=kv,
                            kv_layout=kv_layout, weight_layout=layout)
         with Session(w, seed=29, layers=[0]) as s:
