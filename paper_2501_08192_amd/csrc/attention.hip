@@ -734,9 +734,12 @@ __global__ __launch_bounds__(256, PREP ? 2 : 1) void k_attn(AttnArgs a)
 // at a span's end or a missing block needs stands behind one branch a tile, and the next tile is requested into the registers that
 // the scores (keys) and the second contraction (values) have just read.  Event times: that case 15.8 -> 14.5 us, batch 64 of 8k tokens
 // 34.1 -> 32.1, batch 8 of 4k 6.9 -> 6.2, one sequence of 16k 8.8 -> 8.2.
+// Two workgroups a CU in both forms, as attn_split counts on: left a register budget of 512 the form that prepares its own queries
+// took 264, one workgroup a CU and two rounds for 257-448 of them (now 215).  Eight layers: eight kv heads, one sequence of 12k
+// tokens 292 -> 262 us, two of 20k with two kv heads 413 -> 388.
 
 template <bool PREP>
-__global__ __launch_bounds__(256, PREP ? 2 : 1) void k_attn_q8(AttnArgs a)
+__global__ __launch_bounds__(256, 2) void k_attn_q8(AttnArgs a)
 {
     constexpr int TT = kAttnTileTokensInt8;
     __shared__ float ms[kAttnWaves][16], ls[kAttnWaves][16];
