@@ -808,6 +808,12 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void k_gemm_sk_i8(GemmI8Args 
         }
     };
 
+    // One batch tile, non-temporal loads: the next requests stay behind a block's products.  Mixed with them they need 174 registers
+    // where three workgroups a CU leave 168 (17 spilled to scratch); apart, 132.  Eight layers, no windows, microseconds, spilled / two
+    // workgroups a CU / apart: 70B-shaped TP=8, batch 8 478 / 438 / 431-439; 8B-shaped TP=4, batch 5 375 / 355 / 350; 32 layers of the
+    // 8B-shaped TP=8 shard at batch 16 1388 / 1370 / 1364.
+    auto fence = [] { if constexpr (TILED && NB == 1) __builtin_amdgcn_sched_barrier(0); };
+
     int kb = k0;
     if (held) {     // the blocks held on chip, in the order of the range; ring slots are refilled with the block HS further on
 #pragma unroll
@@ -837,6 +843,7 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void k_gemm_sk_i8(GemmI8Args 
             const int k = kb + q, buf = q & 1;      // (k - k0) & 1, because PF and the number of blocks held are even
             load_x(k + XD, xr[q % XD]);
             mfma_block(buf, wq[q]);
+            fence();
             load_w(k + PF, wq[q]);
             store_x(buf ^ 1, xr[(q + 1) % XD]);
             __syncthreads();
@@ -864,6 +871,7 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void k_gemm_sk_i8(GemmI8Args 
                 const int k = kb + q, buf = q & 1;
                 load_x(min(k + XD, k1 - 1), xr[q % XD]);
                 mfma_block(buf, wq[q]);
+                fence();
                 load_w(min(k + PF, k1 - 1), wq[q]);
                 store_x(buf ^ 1, xr[(q + 1) % XD]);
                 __syncthreads();
@@ -876,6 +884,7 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void k_gemm_sk_i8(GemmI8Args 
             if (k < k1) {
                 const int buf = q & 1;
                 mfma_block(buf, wq[q]);
+                fence();
                 if (k + 1 < k1) store_x(buf ^ 1, xr[(q + 1) % XD]);
                 __syncthreads();
             }

@@ -1,5 +1,6 @@
 """What the compiler gave the kernels of the built library, read from its code objects' own metadata: registers that the launch rules
 count on, and no scratch memory in the kernels of the main path."""
+import os
 import struct
 import subprocess
 
@@ -41,13 +42,13 @@ def _notes(elf):
 @pytest.fixture(scope="module")
 def kernels():
     found = {}
-    for image in _code_objects(open(build.build(force=False), "rb").read()):
+    for image in _code_objects(open(build.LIB if os.path.exists(build.LIB) else build.build(), "rb").read()):
         for note in _notes(image):
             for k in msgpack.unpackb(note)["amdhsa.kernels"]:
                 found[k[".name"]] = k
     names = list(found)
     text = subprocess.run(["c++filt"], input="\n".join(names), text=True, capture_output=True, check=True).stdout.split("\n")
-    return {t.split("(")[0].removeprefix("void psv::"): found[n] for t, n in zip(text, names)}
+    return {t.split("(")[0].removeprefix("void ").removeprefix("psv::"): found[n] for t, n in zip(text, names)}
 
 
 def _group(kernels, name):
@@ -61,3 +62,9 @@ def test_two_attention_workgroups_a_compute_unit(kernels, name):
     """The split fills the chip with two workgroups of four waves a compute unit: 512 registers a lane and SIMD, 160 KiB of LDS."""
     for n, k in _group(kernels, name).items():
         assert k[".vgpr_count"] <= 256 and k[".group_segment_fixed_size"] <= 80 * 1024, n
+
+
+@pytest.mark.parametrize("name", ["k_attn", "k_attn_q8", "k_attn_merge", "k_attn_prep", "k_gemm_sk", "k_gemm_sk_i8", "k_gemv", "k_resid_sum", "k_sk_reduce"])
+def test_no_scratch_in_the_kernels_of_an_operator(kernels, name):
+    for n, k in _group(kernels, name).items():
+        assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, n
