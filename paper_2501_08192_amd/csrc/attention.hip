@@ -958,23 +958,32 @@ __global__ __launch_bounds__(256, 2) void k_attn_q8(AttnArgs a)
 #pragma unroll
             for (int m = 0; m < 4; ++m) { blank4(bad_v, vsc[m]); blank4(bad_v, vc[m]); blank4(bad_v, vc[m + 4]); }
         }
-        float tmax = sv[0];
+        float tmax = sv[0], tmin = sv[0];
 #pragma unroll
-        for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, sv[e]);
+        for (int e = 1; e < 16; ++e) {
+            tmax = fmaxf(tmax, sv[e]);
+            tmin = fminf(tmin, sv[e]);
+        }
         tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
         tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
         const float m_new = fmaxf(m_run, tmax);
-        const float alpha = exp2_raw(m_run - m_new);
+        const float alpha = exp2f(m_run - m_new);
         float pv[16], psum = 0.f, pmax = 0.f;
+        if (__any(tmin < m_new - 126.f)) {          // a probability below 2^-126 counts where its value scale is that much larger
+#pragma unroll
+            for (int e = 0; e < 16; ++e) pv[e] = exp2f(sv[e] - m_new);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) pv[e] = exp2_raw(sv[e] - m_new);
+        }
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             const float vv4[4] = {vsc[m].x, vsc[m].y, vsc[m].z, vsc[m].w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int e = 4 * m + j;
-                const float p = exp2_raw(sv[e] - m_new);
-                psum += p;
-                pv[e] = p * vv4[j];
+                psum += pv[e];
+                pv[e] *= vv4[j];
             }
         }
         if (ragged) {

@@ -174,8 +174,8 @@ __device__ __forceinline__ void two_digits(float t, float &m1, float &m2)
 // 254 * D1 + D2 of a pair of exact digit sums, |D1| < 2^23: one 24-bit multiply-add
 __device__ __forceinline__ int mad_digits(int d1, int d2) { return __mul24(d1, 254) + d2; }
 
-// 2^x by the hardware instruction alone: exp2f's result, except that one below 2^-126 is zero (exp2f scales its argument for it, four
-// more instructions).  For probabilities that are cut into digits of their tile's largest, where that is nothing.
+// 2^x by the hardware instruction alone: exp2f's result for x >= -126 (below, exp2f scales its argument, four more instructions, and
+// this one returns zero).
 __device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Maximum over aligned groups of 32 lanes, returned in every lane of the group (all lanes must be active).
