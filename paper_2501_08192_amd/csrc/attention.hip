@@ -1115,7 +1115,10 @@ __global__ __launch_bounds__(W * 64) void k_attn_merge(AttnArgs a)
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = piece(sp + u * W, nc);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {                      // past the chunks: the last one again, times zero
+        for (int u = 1; u < 8; ++u)                        // past the chunks: the last one again, which may be an infinity
+            if (sp + u * W >= nc) v[u] = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
             num.x = fmaf(wl[w][sp + u * W], v[u].x, num.x);
             num.y = fmaf(wl[w][sp + u * W], v[u].y, num.y);
         }
@@ -1194,7 +1197,7 @@ hipError_t launch_attn_merge(const float *part_ml, const float *part_o, int batc
                            const_cast<float *>(part_o), out_f32, out_bf16);
     a.out_digits = digits ? 1 : 0;
     if (plan) a.plan = *plan;
-    // eight waves where a sequence can have more than 64 chunks (16 rounds of the loop at most), else four
+    // eight waves where a sequence can have more than 64 chunks, else four: four rounds of the loop at most, or two
     const bool many = (plan ? plan->max_chunks : sp.n_chunks) > 64;
     const dim3 grid(nq / nkv, nkv, batch);
     if (plan && many) PSV_LAUNCH((k_attn_merge<true, 8>), grid, dim3(512), 0, s, a);

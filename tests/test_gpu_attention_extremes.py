@@ -52,3 +52,21 @@ def test_probabilities_below_the_normal_range_count_int8(batch, at):
         for b in range(batch):
             ref = torch.softmax(kd[b] @ qkv[b, :128] * 128 ** -0.5, 0) @ vd[b]
             assert float((got[b] - ref).norm() / ref.norm()) < 2e-3, b
+
+
+@pytest.mark.parametrize("kv", ["bf16", "int8"])
+@pytest.mark.parametrize("batch,context", [(1, 6000), (1, 20000), (3, 6000), (3, 20000)])      # four and eight waves a merge, both forms
+def test_an_overflowing_sum_stays_an_infinity(batch, context, kv):
+    """Values of 3e38 whose sums leave the range, in more chunks than the merge requests at once: infinite, as each chunk's sum is."""
+    w = synth.Workload("huge", 1, 512, 1, 1, 128, 256, batch, context, False, (0.0, 0.0), kv_format=kv)
+    with Session(w, seed=43, fused=0) as s:
+        s.k_pools[0].zero_()
+        if kv == "bf16":
+            s.v_pools[0].fill_(3e38)
+        else:
+            v = s.v_pools[0].cpu()
+            v[..., :2048] = 127
+            v[..., 2048:] = torch.full((16,), 2.4e36, dtype=torch.float32).view(torch.uint8).view(v.dtype)
+            s.v_pools[0].copy_(v)
+        got = _attention(s, batch, 1)
+        assert bool((got == float("inf")).all()), got[:, :4]
