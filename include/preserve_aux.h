@@ -122,6 +122,9 @@ psv_status psv_debug_last_step_path(psv_ctx *ctx, uint32_t *path);
 /* How many first consumers the most recent psv_decode_step launched into their communication windows (policy.prelaunch;
  * per-operator and per-block kernels -- the whole-step kernel has its windows inside and reports 0). */
 psv_status psv_debug_last_step_prelaunches(psv_ctx *ctx, uint32_t *count);
+/* What the most recent psv_decode_step read as data that will have left the memory-side cache (non-temporal loads, in the kernels that
+ * have that form): bit 0 weights, bit 1 keys and values.  Results do not depend on it. */
+psv_status psv_debug_last_step_read_once(psv_ctx *ctx, uint32_t *what);
 
 /* Intermediate buffers of the most recent layer executed, for debugging parity failures.  PSV_DBG_H1 and
  * PSV_DBG_H2 exist only when the step ran on the vector path (batch 1, or batch 2 with H <= 4096): the

@@ -32,7 +32,7 @@ EXPORTS = [
     "psv_check_overlap",
     "psv_set_profile_op",
     "psv_get_profile", "psv_prefetch_region", "psv_spin", "psv_copy_bytes", "psv_debug_read",
-    "psv_debug_force_wait_timeout", "psv_decode_step_static", "psv_set_fused_kernels", "psv_debug_last_step_path", "psv_debug_last_step_prelaunches", "psv_tile_weights",
+    "psv_debug_force_wait_timeout", "psv_decode_step_static", "psv_set_fused_kernels", "psv_debug_last_step_path", "psv_debug_last_step_prelaunches", "psv_debug_last_step_read_once", "psv_tile_weights",
 ]
 
 
@@ -121,6 +121,7 @@ def lib():
             "psv_debug_force_wait_timeout": (C.c_int32, [vp, u32]),
             "psv_debug_last_step_path": (C.c_int32, [vp, C.POINTER(u32)]),
             "psv_debug_last_step_prelaunches": (C.c_int32, [vp, C.POINTER(u32)]),
+            "psv_debug_last_step_read_once": (C.c_int32, [vp, C.POINTER(u32)]),
             "psv_tile_weights": (C.c_int32, [vp, vp, u32, u32, u32, vp]),
             "psv_set_fused_kernels": (C.c_int32, [vp, u32]),
             "psv_decode_step_static": (C.c_int32, [C.POINTER(psv_model_desc), C.POINTER(psv_layer_weights),
@@ -335,6 +336,13 @@ def psv_debug_last_step_prelaunches(ctx):
     out = C.c_uint32(0)
     _check(lib().psv_debug_last_step_prelaunches(ctx, C.byref(out)), "psv_debug_last_step_prelaunches")
     return int(out.value)
+
+
+def psv_debug_last_step_read_once(ctx):
+    """(weights, keys and values): read non-temporally in the last step?"""
+    out = C.c_uint32(0)
+    _check(lib().psv_debug_last_step_read_once(ctx, C.byref(out)), "psv_debug_last_step_read_once")
+    return bool(out.value & 1), bool(out.value & 2)
 
 
 def psv_debug_force_wait_timeout(ctx, on):

@@ -207,6 +207,13 @@ psv_status psv_debug_last_step_prelaunches(psv_ctx *c, uint32_t *count)
     return PSV_OK;
 }
 
+psv_status psv_debug_last_step_read_once(psv_ctx *c, uint32_t *what)
+{
+    if (!c || !what) return PSV_ERR_INVALID_ARG;
+    *what = c->last_step_once;
+    return PSV_OK;
+}
+
 psv_status psv_set_fused_kernels(psv_ctx *c, uint32_t on)
 {
     if (!c || on > 3) return PSV_ERR_INVALID_ARG;

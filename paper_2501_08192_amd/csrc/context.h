@@ -53,6 +53,7 @@ struct psv_ctx {
     uint32_t last_prefetch_launches = 0;
     uint32_t step_launches = 0, step_layers = 0; // launches of the operator chain in the last step (windows included), and its layers
     uint32_t last_step_prelaunches = 0;          // consumers the last step launched into their windows
+    uint32_t last_step_once = 0;                 // what it read non-temporally: bit 0 weights, bit 1 keys and values
     unsigned window_seq = 0;                     // sequence number of the last communication window enqueued
     uint32_t attn_chunk_tokens = 0;               // 0 = default split; else tokens per attention workgroup (psv_set_attention_chunk, psv_tune_attention)
     bool attn_tuning = false;                    // psv_tune_attention is timing candidates: every step makes the list of its lengths, used or not

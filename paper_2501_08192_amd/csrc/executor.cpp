@@ -74,22 +74,24 @@ Workspace layout_workspace(const psv_model_desc &d)
     return w;
 }
 
-// Bytes a step reads at most, against the memory-side cache's 256 MB: what exceeds it is not there any more in the next step.
-static bool read_once(const psv_model_desc &d, bool with_cache)
+// Bytes a step reads -- the weights, with a batch its cache too at the planned context (the longest there is while no policy is set) --
+// against the memory-side cache's 256 MB: what exceeds it is not there any more in the next step.
+static bool read_once(const psv_ctx *c, uint32_t batch)
 {
-    uint64_t layer = with_cache ? op_mem_size(d, PSV_OP_ATTN, d.max_batch, d.max_seq) : 0;
+    const psv_model_desc &d = c->d;
+    uint64_t layer = batch ? op_mem_size(d, PSV_OP_ATTN, batch, c->plan_context ? c->plan_context : d.max_seq) : 0;
     for (uint32_t o : {PSV_OP_QKV, PSV_OP_O, PSV_OP_GATE, PSV_OP_UP, PSV_OP_DOWN}) layer += op_mem_size(d, o, 1, 1);
     return d.n_layers * layer > 256u << 20;
 }
 
-KvView kv_view(const psv_ctx *c, uint32_t layer)
+KvView kv_view(const psv_ctx *c, uint32_t layer, uint32_t batch)
 {
     KvView v;
     v.k_pool = static_cast<uint16_t *>(c->k_pools[layer]);
     v.v_pool = static_cast<uint16_t *>(c->v_pools[layer]);
     v.int8 = c->d.kv_format == PSV_FMT_INT8 ? 1 : 0;
     v.token_major = c->d.kv_layout == PSV_KV_TOKEN_MAJOR ? 1 : 0;
-    v.once = read_once(c->d, true) ? 1 : 0;
+    v.once = read_once(c, batch) ? 1 : 0;
     v.page_table = c->kv.page_table;
     v.max_blocks = (int)c->kv.max_blocks;
     {
@@ -150,7 +152,7 @@ Mat mat_of(const psv_ctx *c, const psv_layer_weights &w, uint32_t op)
     default: break;
     }
     m.tiled = c->d.weight_layout == PSV_W_TILED;
-    m.once = read_once(c->d, false);
+    m.once = read_once(c, 0);
     m.warm = c->policy.mode == 1;
     return m;
 }
@@ -237,7 +239,7 @@ psv_status add_entry(psv_ctx *c, JobBuilder &jb, const psv_plan_entry &e, uint32
         const uint64_t total = (uint64_t)batch * blocks_per_seq;
         uint64_t count = (e.bytes + bytes_per_block - 1) / bytes_per_block;
         if (count > total) count = total;
-        jb.add_kv(kv_view(c, e.target_layer), (int)c->d.n_kv_heads, blocks_per_seq, count, bytes_per_block);
+        jb.add_kv(kv_view(c, e.target_layer, batch), (int)c->d.n_kv_heads, blocks_per_seq, count, bytes_per_block);
         return jb.st;
     }
     const char *p = static_cast<const char *>(weight_ptr(c->weights[e.target_layer], e.target_op));
@@ -390,7 +392,7 @@ static psv_status enqueue_whole_step(psv_ctx *c, const float *x_in, float *x_out
         HIP_TRY(hipMemcpyAsync(c->wsp + c->ws.step_tbl, c->step_tbl_host.data(), c->step_tbl_host.size(), hipMemcpyHostToDevice, s));
         c->step_tbl_dirty = false;
     }
-    const KvView kv = kv_view(c, lb);
+    const KvView kv = kv_view(c, lb, 1);
     float2 *rope = c->at<float2>(c->ws.rope);
     const double *inv_freq = d.rope_theta > 0.f ? c->at<double>(c->ws.inv_freq) : nullptr;
     c->last_prefetch_launches = 0;
@@ -481,6 +483,7 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
                      gemv_supported(B, F, H) && gemv_supported(B, H, F);
     const bool sk = !vec;
     c->last_step_vec = vec;
+    c->last_step_once = (read_once(c, 0) ? 1u : 0u) | (read_once(c, batch) ? 2u : 0u);
     // Which kernels run depends on the shape and the caller's setting only, never on the policy, so every policy gives
     // the same bits.  Left to the library (3), the per-block kernels are used where they are the faster way to run with
     // prefetching on: rows of at least 4096 elements and blocks whose weights all fit the registers of one pass, so that
@@ -557,12 +560,12 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
     c->last_step_planned = plan != nullptr;
 
     ST_TRY(prof_tag(c, -2));
-    HIP_TRY(launch_rope_table(c->kv.seq_lens, inv_freq, kv_view(c, lb).max_tokens, B, rope, made, s));
+    HIP_TRY(launch_rope_table(c->kv.seq_lens, inv_freq, kv_view(c, lb, batch).max_tokens, B, rope, made, s));
     const float *res = x_in, *delta = nullptr;   // residual stream entering the layer = res + delta
     int delta_splits = 1;                        // delta may be a stack of split-K partials
     for (uint32_t l = lb; l < le; ++l) {
         const psv_layer_weights &w = c->weights[l];
-        const KvView kv = kv_view(c, l);
+        const KvView kv = kv_view(c, l, batch);
         const Mat Wqkv = mat_of(c, w, PSV_OP_QKV), Wo = mat_of(c, w, PSV_OP_O), Wg = mat_of(c, w, PSV_OP_GATE),
                   Wu = mat_of(c, w, PSV_OP_UP), Wd = mat_of(c, w, PSV_OP_DOWN);
 

@@ -43,7 +43,8 @@ struct KvView {
     uint16_t *v_pool;
     int int8;
     int token_major;             // bf16 pools laid out [block][16 tokens][kv head][128] (both K and V)
-    int once;                    // weights and the largest cache together exceed the memory-side cache (Mat::once)
+    int once;                    // weights and the cache of the step's batch at the planned context exceed the memory-side cache (Mat::once); the lengths
+                                 //   themselves are on the device: shorter ones than planned are not seen
     const int32_t *page_table;   // null => contiguous
     int max_blocks;
     int max_tokens;              // longest valid sequence: min(max_blocks * 16, the descriptor's max_seq); the

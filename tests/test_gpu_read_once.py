@@ -4,6 +4,7 @@ bits, on the vector path, with one to four batch tiles, for every layout, and la
 import pytest
 import torch
 
+from paper_2501_08192_amd import binding as psv
 from paper_2501_08192_amd import synth
 from paper_2501_08192_amd.harness import Session, default_policy
 
@@ -30,3 +31,20 @@ def test_same_bits_as_the_only_layer_and_as_the_first_of_many(batch, weights, kv
     assert torch.isfinite(outs[0][0]).all() and torch.equal(outs[0][0], outs[0][1])
     for a, b in zip(*outs):
         assert torch.equal(a.view(torch.int16) if a.dtype == torch.bfloat16 else a, b.view(torch.int16) if b.dtype == torch.bfloat16 else b)
+
+
+def test_the_cache_counts_as_far_as_it_is_read():
+    """Weights fit the memory-side cache, the largest cache the context can hold does not: keys and values are read that way for a step
+    whose planned context and batch exceed it, not for a short one of the same context, and the bits are the same."""
+    w = synth.Workload("live", 4, 1024, 8, 8, 128, 1024, 16, 4096, False, (0.0, 0.0))      # 60 MB of weights, up to 1 GiB of cache
+    with Session(w, seed=3) as s:
+        outs = []
+        for context, batch, want in ((4096, 16, True), (700, 16, False), (4096, 2, False), (16, 1, False), (900, 16, True)):
+            psv.psv_set_policy(s.ctx, psv.prefetch_policy(mode=0), batch, context)
+            s.seq_lens.fill_(16)
+            psv.psv_decode_step(s.ctx, s.x_in, s.x_out, batch, 0, w.n_layers)
+            s.sync()
+            assert psv.psv_debug_last_step_read_once(s.ctx) == (False, want), (context, batch)
+            if batch == 16:
+                outs.append(s.x_out.clone())
+        assert all(torch.equal(o, outs[0]) for o in outs)
