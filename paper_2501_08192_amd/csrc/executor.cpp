@@ -153,7 +153,6 @@ Mat mat_of(const psv_ctx *c, const psv_layer_weights &w, uint32_t op)
     }
     m.tiled = c->d.weight_layout == PSV_W_TILED;
     m.once = read_once(c, 0);
-    m.warm = c->policy.mode == 1;
     return m;
 }
 

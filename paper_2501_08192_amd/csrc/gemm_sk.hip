@@ -618,9 +618,9 @@ constexpr int kSkI8Blocks = 18;    // most 128-element blocks of a waiting workg
 // (16 KiB each), on chip.  The operand's block scales share cache lines between producer workgroups of different XCDs,
 // so the waiting variant reads those of its K range with device-coherent loads, once, after the wait.
 // TILED: as for k_gemm_sk, where the weights do not stay in the memory-side cache.  Four layers, no windows / cache-only, microseconds: 70B-shaped
-// TP=8, batch 8 241 -> 221 / 379 -> 371, batch 32 272 -> 262 / 417 -> 413; TP=4 batch 16 301 -> 286 / 448 -> 440, batch 64 467 -> 450 / 606 -> 604.  One batch tile
-// keeps the ordinary loads where windows prefetch: out of the memory-side cache they are the faster ones (batch 8 launched into its
-// windows, eight layers 732 / 744).
+// TP=8, batch 32 272 -> 262 / 417 -> 413; TP=4 batch 64 467 -> 450 / 606 -> 604.  One batch tile, where windows of 20 us prefetch too: 70B-shaped TP=8,
+// batch 8, eight layers, cache-only 768 -> 748, launched ahead 742 / 741, windows of 0 454 -> 434; 8B-shaped TP=4, batch 5 699 -> 681 and
+// 687 / 691; 70B-shaped TP=4, batch 16, four layers 529 -> 518 and 514 / 515.
 template <int NB, int HOLD, bool TILED = false>
 __global__ __launch_bounds__(256, NB == 1 ? 3 : 2) void k_gemm_sk_i8(GemmI8Args a, PrefetchJob pj)
 {
@@ -1108,7 +1108,7 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
             return hipGetLastError();
         }
         auto go8 = [&](auto kernel, auto kernel_once) {
-            if (W.tiled && W.once && !(nb == 1 && W.warm)) PSV_LAUNCH(kernel_once, grid, dim3(256), 0, s, q, PrefetchJob{});
+            if (W.tiled && W.once) PSV_LAUNCH(kernel_once, grid, dim3(256), 0, s, q, PrefetchJob{});
             else PSV_LAUNCH(kernel, grid, dim3(256), 0, s, q, PrefetchJob{});
             return hipGetLastError();
         };

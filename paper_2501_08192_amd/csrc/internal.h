@@ -65,7 +65,6 @@ struct Mat {
     const float *scale = nullptr;
     bool tiled = false;          // PSV_W_TILED storage (matrix-core projections only)
     bool once = false;           // the model's weights do not fit the memory-side cache: nothing of them is there in the next step
-    bool warm = false;           // ... but a window's prefetch may have put it there in this one
 };
 
 // ---- kernel launchers ---------------------------------------------------------------------
