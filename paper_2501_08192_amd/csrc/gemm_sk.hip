@@ -612,7 +612,7 @@ struct GemmI8Args {
     SkWaitArgs wt;                 // k_gemm_sk_i8<1, HOLD>, HOLD > 0
 };
 
-constexpr int kSkI8Blocks = 18;    // most 128-element blocks of a waiting workgroup (gemm_sk_splits)
+constexpr int kSkI8Blocks = 18;    // most 128-element blocks of a waiting workgroup: what gemm_sk_can_wait admits, launch_gemm_sk refuses more
 
 // HOLD, pj: as for k_gemm_sk.  The waiting variant keeps the 4 blocks of its register ring, or those and 2 more in LDS
 // (16 KiB each), on chip.  The operand's block scales share cache lines between producer workgroups of different XCDs,
@@ -1067,6 +1067,7 @@ bool gemm_sk_can_wait(int batch, int N, int K, bool w8, bool tiled, int cus)
         const int hs = w8 ? (lv ? 12 : 8) : nb == 2 ? (lv ? 8 : 6) : (lv ? 12 : 6);
         if (hs * 3 < spb) return false;
     }
+    if (w8 && spb > 2 * kSkI8Blocks) return false;
     // ... and it is the window's prefetch kernel as well, which needs at least 128 workgroups to reach its rate
     if (grid < 128 || grid > (long long)r.occ[kind][lv] * cus) return false;
     const bool free_slots = grid + cus / 4 <= (long long)r.occ[kind][lv] * cus;
@@ -1091,6 +1092,7 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
     };
     if (wait && (!ssq || !wait->ssq_ll || !wait->win_done || batch > (W.scale ? 16 : kSkWaitMaxBatch) || K % 512 || (long long)batch * (K / 512) > kSkWaitEntries)) return hipErrorInvalidValue;
     if (W.scale) {   // int8 weights: xb holds digit planes (bytes), see k_gemm_sk_i8
+        if (K % 128) return hipErrorInvalidValue;       // whole blocks
         GemmI8Args q{};
         q.W = static_cast<const int8_t *>(W.w); q.W2 = static_cast<const int8_t *>(W2.w ? W2.w : W.w);
         q.scale = W.scale; q.scale2 = W2.w ? W2.scale : W.scale; q.split_row = W2.w ? split_row : N;
@@ -1099,6 +1101,7 @@ hipError_t launch_gemm_sk(Mat W, Mat W2, int split_row, const uint16_t *xb, cons
         q.tiled = W.tiled ? 1 : 0;
         const int splits = gemm_sk_splits(batch, N, K, true, W.tiled, W2.w != nullptr);
         q.blocks_per_wg = (q.n_blocks + splits - 1) / splits;
+        if (wait && q.blocks_per_wg > kSkI8Blocks) return hipErrorInvalidValue;     // the waiting kernel's table of scales
         const dim3 grid((N + 127) / 128, splits);
         if (wait) {
             fill_wait(q.wt, q.blocks_per_wg);

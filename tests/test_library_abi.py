@@ -99,6 +99,32 @@ def test_null_and_range_arguments_are_rejected_without_a_gpu():
     assert psv.psv_validate_desc(bad_layout) == psv.PSV_ERR_INVALID_ARG
 
 
+def test_int8_projection_refuses_what_its_kernels_cannot_hold():
+    """launch_gemm_sk (an internal function, found by its C++ name): columns that are not whole blocks of 128, and a launch into a
+    window with ranges longer than the waiting kernel's table of scales, are refused before anything is launched."""
+    class Mat(C.Structure):
+        _fields_ = [("w", C.c_void_p), ("scale", C.c_void_p), ("tiled", C.c_bool), ("once", C.c_bool)]
+
+    class Wait(C.Structure):
+        _fields_ = [("ssq_ll", C.c_void_p), ("tag", C.c_uint), ("win_done", C.c_void_p), ("win_seq", C.c_uint), ("iters", C.c_uint32),
+                    ("ticks", C.c_uint64), ("err", C.c_void_p), ("share_w", C.c_double), ("share_w2", C.c_double), ("job", C.c_void_p)]
+
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("a GPU is present")
+    launch = getattr(psv.lib(), "_ZN3psv14launch_gemm_skENS_3MatES0_iPKtPKffPfiiiPKNS_6SkWaitEP12ihipStream_t")
+    launch.restype = C.c_int
+    launch.argtypes = [Mat, Mat, C.c_int, C.c_void_p, C.c_void_p, C.c_float, C.c_void_p, C.c_int, C.c_int, C.c_int, C.POINTER(Wait), C.c_void_p]
+    m, wait = Mat(4096, 4096, False, False), Wait(4096, 1, 4096, 1, 0, 0, 4096, 0.0, 0.0, None)
+
+    def status(k, w):
+        return launch(m, m, 256, 4096, 4096, 1e-5, 4096, 1, 512, k, C.byref(w) if w else None, None)
+
+    invalid = 1
+    assert status(192, None) == invalid and status(65536, wait) == invalid
+    assert status(256, None) != invalid and status(4096, wait) != invalid        # these get as far as the missing device
+
+
 def test_create_fails_cleanly_without_a_gpu():
     import torch
     if torch.cuda.is_available():
