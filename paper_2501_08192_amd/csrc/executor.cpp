@@ -617,7 +617,7 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
         } else if (fuse_merge) {
             HIP_TRY(launch_gemv_merge(Wo, pml, po, nq, nkv, sp.n_chunks, attn, delta_a, B, H, s));
         } else if (vec) {
-            HIP_TRY(launch_gemv(Wo, Mat{}, attn, delta_a, B, H, QD, s));
+            HIP_TRY(launch_gemv(Wo, attn, delta_a, B, H, QD, s));
         } else {
             if (!gemm_sk_supported(B, H, QD)) return PSV_ERR_UNSUPPORTED;
             HIP_TRY(launch_gemm_sk(Wo, Mat{}, 0, attnb, nullptr, 0.f, part, B, H, QD, nullptr, s));
@@ -663,7 +663,7 @@ psv_status enqueue_step(psv_ctx *c, const float *x_in, float *x_out, uint32_t ba
         delta_splits = 1;
         if (seg_mlp) {
         } else if (vec) {
-            HIP_TRY(launch_gemv(Wd, Mat{}, m, delta_m, B, H, F, s));
+            HIP_TRY(launch_gemv(Wd, m, delta_m, B, H, F, s));
         } else {
             if (!gemm_sk_supported(B, H, F)) return PSV_ERR_UNSUPPORTED;
             HIP_TRY(launch_gemm_sk(Wd, Mat{}, 0, mb, nullptr, 0.f, part, B, H, F, nullptr, s));

@@ -486,8 +486,8 @@ static hipError_t gemv_go(GemvArgs a, hipStream_t s)
     // pass (29 MB at batch 2 11.7 / 11.9); rows longer than 4096 take one workgroup a CU all the same (59 MB 19.0 -> 18.3, 117 MB
     // 34.0 -> 32.3).  A matrix of a single pass keeps the spread.
     if constexpr (SW && MODE == GEMV_NORM) {
-        constexpr int BUF = W8 ? 1 : 2, OCC = ITERS == 1 ? 4 : 2;
-        if constexpr (RB * BUF == 8 && (ITERS == 2 ? NB == 1 : !W8)) {
+        constexpr int BUF = W8 ? 1 : 2, OCC = W8 ? 1 : ITERS == 1 ? 4 : 2;     // int8: the ordinary kernel in another geometry
+        if constexpr (RB * BUF == 8 && (ITERS == 2 || !W8)) {
             const GemvGeom g2 = gemv_geom(a.N, a.K, ITERS, threads, 8, ITERS == 1 ? 512 : 256);
             if (g2.max_rows > RB) {
                 a.passes = (g2.max_rows + RB - 1) / RB;
@@ -521,13 +521,16 @@ static hipError_t gemv_pick(const GemvArgs &a, hipStream_t s)
 {
     const int threads = gemv_threads(MODE);
     const bool sw = a.W2 != nullptr, two = a.K > 8 * threads;
-    if (MODE == GEMV_MERGE && sw) return hipErrorInvalidValue;   // the merge prologue feeds the O projection only
-    if (a.scale) {
-        if (two) return sw ? gemv_rows<NB, 2, MODE != GEMV_MERGE, MODE, true>(a, s) : gemv_rows<NB, 2, false, MODE, true>(a, s);
-        return sw ? gemv_rows<NB, 1, MODE != GEMV_MERGE, MODE, true>(a, s) : gemv_rows<NB, 1, false, MODE, true>(a, s);
+    constexpr bool SW = MODE == GEMV_NORM;                  // gate | up is the only pair, and it opens a block
+    if (sw && !SW) return hipErrorInvalidValue;
+    if (two) {
+        // two sequences take this path on rows of at most 4096 elements: no normalised projection of theirs has longer ones
+        if constexpr (SW && NB == 2) return hipErrorInvalidValue;
+        else if (a.scale) return sw ? gemv_rows<NB, 2, SW, MODE, true>(a, s) : gemv_rows<NB, 2, false, MODE, true>(a, s);
+        else return sw ? gemv_rows<NB, 2, SW, MODE, false>(a, s) : gemv_rows<NB, 2, false, MODE, false>(a, s);
     }
-    if (two) return sw ? gemv_rows<NB, 2, MODE != GEMV_MERGE, MODE, false>(a, s) : gemv_rows<NB, 2, false, MODE, false>(a, s);
-    return sw ? gemv_rows<NB, 1, MODE != GEMV_MERGE, MODE, false>(a, s) : gemv_rows<NB, 1, false, MODE, false>(a, s);
+    if (a.scale) return sw ? gemv_rows<NB, 1, SW, MODE, true>(a, s) : gemv_rows<NB, 1, false, MODE, true>(a, s);
+    return sw ? gemv_rows<NB, 1, SW, MODE, false>(a, s) : gemv_rows<NB, 1, false, MODE, false>(a, s);
 }
 
 template <int MODE>
@@ -540,10 +543,10 @@ static hipError_t gemv_dispatch(const GemvArgs &a, int batch, hipStream_t s)
     }
 }
 
-hipError_t launch_gemv(Mat W, Mat W2, const float *x, float *out, int batch, int N, int K, hipStream_t s)
+hipError_t launch_gemv(Mat W, const float *x, float *out, int batch, int N, int K, hipStream_t s)
 {
     GemvArgs a{};
-    a.W = W.w; a.W2 = W2.w; a.once = W.once; a.scale = W.scale; a.scale2 = W2.scale; a.x = x; a.out = out; a.N = N; a.K = K;
+    a.W = W.w; a.once = W.once; a.scale = W.scale; a.x = x; a.out = out; a.N = N; a.K = K;
     return gemv_dispatch<GEMV_PLAIN>(a, batch, s);
 }
 

@@ -73,9 +73,9 @@ struct Mat {
 void set_launch_events(hipEvent_t start, hipEvent_t stop);
 
 // Vector-ALU GEMV for batch <= 2:  out[b][r] = sum_k W[r][k] * x[b][k]   (fp32 x; W bf16 or int8 + row scale).
-// W2.w != null selects the SwiGLU form: out[b][r] = silu(W[r].x[b]) * (W2[r].x[b]); same format as W.
-hipError_t launch_gemv(Mat W, Mat W2, const float *x, float *out, int batch, int N, int K, hipStream_t s);
-// Same with the activations formed in the prologue: x = rmsnorm(res + delta) * gain.  out_res
+hipError_t launch_gemv(Mat W, const float *x, float *out, int batch, int N, int K, hipStream_t s);
+// Same with the activations formed in the prologue: x = rmsnorm(res + delta) * gain (two sequences: rows of at most 4096 elements).
+// W2.w != null selects the SwiGLU form: out[b][r] = silu(W[r].x[b]) * (W2[r].x[b]); same format as W.  out_res
 // receives res + delta and out_h (optional) the normalised vector; neither may alias res or delta.
 // wait != null: the kernel is launched before its inputs exist.  It requests its first weights, then waits
 // (bounded) until *done has reached seq -- published by the window kernel when the window ends -- and only

@@ -51,6 +51,14 @@ def kernels():
     return {t.split("(")[0].removeprefix("void ").removeprefix("psv::"): found[n] for t, n in zip(text, names)}
 
 
+def test_no_projection_kernel_that_nothing_launches(kernels):
+    """k_gemv<batch, rows a pass, loads a row, pair, prologue, ...>: pairs are normalised (prologue 1), and two sequences have normalised
+    rows of one load only."""
+    for n in _group(kernels, "k_gemv"):
+        batch, _, loads, pair, prologue = n[len("k_gemv<"):-1].split(", ")[:5]
+        assert not (pair == "true" and prologue != "1") and not (batch == "2" and loads == "2" and prologue == "1"), n
+
+
 def _group(kernels, name):
     some = {n: k for n, k in kernels.items() if n == name or n.startswith(name + "<")}
     assert some, name
