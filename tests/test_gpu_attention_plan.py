@@ -25,7 +25,9 @@ EDGES = [1, 2, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257]
     (64, 8, 1, 300, [1] * 63 + [300]),              # fewer places than sequences: one chunk each
     (3, 1, 8, 3000, [7, 3000, 300]),                # most chunks of one sequence
     (5, 1, 2, 3000, [1, 2, 3, 4, 5]),               # nobody near the longest possible length
-], ids=["edges", "b16", "b16_equal", "kv8", "one_chunk_each", "long", "short"])
+    (3, 1, 2, 20000, [20000, 5003, 1500]),          # merged by eight waves: 157 chunks, 40 and 12 (int8 79, 20 and 6)
+    (4, 1, 2, 8100, [8100, 4100, 1030, 129]),       # merged by four: 64, 33, 9 and 2 (int8 32, 17, 5 and 1)
+], ids=["edges", "b16", "b16_equal", "kv8", "one_chunk_each", "long", "short", "merge8", "merge4"])
 @pytest.mark.parametrize("kv", ["bf16", "int8"])
 @pytest.mark.parametrize("paged", [False, True], ids=["contiguous", "paged"])
 def test_split_by_length(batch, nkv, group, context, lens, kv, paged):
