@@ -11,6 +11,23 @@ from paper_2501_08192_amd.harness import Session, default_policy
 pytestmark = pytest.mark.gpu
 
 
+def _same_bits(layers, weights_once, kv_once, *shape, **formats):
+    """Two numbers of layers, the rule's answers for the larger one (none for the smaller), and bits that agree."""
+    outs = []
+    for n_layers in layers:
+        w = synth.Workload("once", n_layers, *shape, (8.0, 8.0), **formats)
+        with Session(w, seed=29, layers=[0]) as s:
+            s.seq_lens.copy_(torch.tensor([w.context - 11 * b for b in range(w.batch)], dtype=torch.int32))
+            out = [s.run().clone()]
+            s.set_policy(default_policy(w, budget_bytes=1 << 40))
+            out.append(s.run().clone())
+            assert psv.psv_debug_last_step_read_once(s.ctx) == ((weights_once, kv_once) if n_layers == layers[1] else (False, False))
+            outs.append(out + [s.k_pools[0].clone(), s.v_pools[0].clone()])
+    assert torch.isfinite(outs[0][0]).all() and torch.equal(outs[0][0], outs[0][1])
+    for a, b in zip(*outs):
+        assert torch.equal(a.view(torch.int16) if a.dtype == torch.bfloat16 else a, b.view(torch.int16) if b.dtype == torch.bfloat16 else b)
+
+
 @pytest.mark.parametrize("batch,weights,kv,layout,kv_layout,paged", [
     (1, "bf16", "bf16", "row", "head", True), (2, "bf16", "bf16", "row", "token", False), (1, "int8", "int8", "row", "head", True),
     (3, "bf16", "bf16", "tiled", "head", True), (17, "bf16", "bf16", "tiled", "token", True), (33, "bf16", "int8", "tiled", "head", False),
@@ -18,19 +35,17 @@ pytestmark = pytest.mark.gpu
     (3, "int8", "bf16", "tiled", "head", False), (17, "int8", "int8", "tiled", "head", True), (64, "int8", "bf16", "tiled", "head", True),
 ])
 def test_same_bits_as_the_only_layer_and_as_the_first_of_many(batch, weights, kv, layout, kv_layout, paged):
-    outs = []
-    for n_layers in (1, 80):           # 11.5 MB a layer in bf16, 5.8 MB in int8
-        w = synth.Workload("once", n_layers, 1024, 8, 2, 128, 1024, batch, 700, paged, (8.0, 8.0), weight_format=weights, kv_format=kv,
-                           kv_layout=kv_layout, weight_layout=layout)
-        with Session(w, seed=29, layers=[0]) as s:
-            s.seq_lens.copy_(torch.tensor([700 - 11 * b for b in range(batch)], dtype=torch.int32))
-            out = [s.run().clone()]
-            s.set_policy(default_policy(w, budget_bytes=1 << 40))
-            out.append(s.run().clone())
-            outs.append(out + [s.k_pools[0].clone(), s.v_pools[0].clone()])
-    assert torch.isfinite(outs[0][0]).all() and torch.equal(outs[0][0], outs[0][1])
-    for a, b in zip(*outs):
-        assert torch.equal(a.view(torch.int16) if a.dtype == torch.bfloat16 else a, b.view(torch.int16) if b.dtype == torch.bfloat16 else b)
+    _same_bits((1, 80), True, True, 1024, 8, 2, 128, 1024, batch, 700, paged,        # 11.5 MB a layer in bf16, 5.8 MB in int8
+               weight_format=weights, kv_format=kv, kv_layout=kv_layout, weight_layout=layout)
+
+
+@pytest.mark.parametrize("batch,weights", [(1, "bf16"), (2, "bf16"), (1, "int8")])
+def test_same_bits_with_two_passes_of_weights_in_flight(batch, weights):
+    _same_bits((1, 8), True, True, 4096, 8, 2, 128, 3584, batch, 100, False, weight_format=weights)       # 109 MB a layer in bf16
+
+
+def test_same_bits_where_only_the_cache_exceeds_it():
+    _same_bits((1, 16), False, True, 1024, 8, 2, 128, 1024, 33, 700, True, weight_layout="tiled")         # 184 MB of weights
 
 
 def test_the_cache_counts_as_far_as_it_is_read():
