@@ -258,9 +258,8 @@ __device__ __forceinline__ uint4 ld16(const uint16_t *p) { return *reinterpret_c
 __device__ __forceinline__ uint4 zero16() { return make_uint4(0u, 0u, 0u, 0u); }
 
 // Loads for data that is read once (non-temporal: the lines are the first to leave the caches).  Split-K and attention partials are
-// such data, and their buffers are written again by the next kernel but one: lines that stay in the caches of the XCDs that read them
-// have to be taken back there before another XCD's store goes through.  Measured on a projection and the kernel that sums it, ordinary loads ->
-// these: 15 MB down at batch 64 12.8 -> 11.2 us, 59 MB at batch 8 13.6 -> 12.2, 17 MB O 7.1 -> 6.5, 6 MB QKV at batch 5 7.0 -> 5.7.
+// such data, in buffers that the next kernel but one writes again.  Why it is faster was not traced; measured on a projection and the
+// kernel that sums it, ordinary loads -> these: 15 MB down at batch 64 12.8 -> 11.2 us, 59 MB at batch 8 13.6 -> 12.2, 17 MB O 7.1 -> 6.5, 6 MB QKV at batch 5 7.0 -> 5.7.
 __device__ __forceinline__ float4 ld_once(const float4 *p)
 {
     const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));

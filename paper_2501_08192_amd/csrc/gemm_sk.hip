@@ -999,8 +999,10 @@ static int sk_range_slabs(int K, int splits, bool w8)
 // same place within 4 KiB at the same time, a sixteenth of the memory channels.  There every row tile starts two slabs (256
 // bytes) further into its range than the one before: 235 MB gate | up, rows of 16 KiB, batch 16 56.1 -> 50.4 us (one slab 50.2, three
 // 49.7).  Other ranges spread by themselves and are walked in order (rows of 14 KiB 22.1 -> 23.4 with a turn, ranges of 15 slabs
-// no difference).  The tiled layout takes the same turn, so that a row's sums have one order in both; it is no slower for it (42.0
-// -> 40.8; with one slab 48.8).  Gate | up only, in kernels of its own: no single matrix of the shards has such ranges, and the wrap
+// no difference).  Four layers of that shard, walked in order -> turned: row-major batch 16 481 -> 474 us, batch 32 552 -> 536, batch 64
+// 643 / 643.  The tiled layout takes the same turn, so that a row's sums have one order in both; it is no slower for it (42.0
+// -> 40.8; with one slab 48.8; batch 16 401 / 400, batch 64 558 / 557).  Ranges that begin at multiples of 2 KiB (70B-shaped TP=8 shard from
+// batch 42 on) are walked in order: row-major 424 / 425 at batch 64, tiled 390 / 385, which is left.  Gate | up only, in kernels of its own: no single matrix of the shards has such ranges, and the wrap
 // costs the others up to 1 us (batch 16 O 7.9 -> 8.7).
 static bool sk_turn(int K, int slabs_per_block) { return K % 2048 == 0 && slabs_per_block % 32 == 0; }
 
