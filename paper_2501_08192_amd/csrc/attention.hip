@@ -343,8 +343,11 @@ __device__ __forceinline__ AttnChunk attn_chunk(const AttnArgs &a, int kvh)
 //    halves of a token in neighbouring rows.  Each half needs its own channels of Q, so every operand is multiplied with both
 //    and a lane adds the two useful rows: twice the score products, on matrix cores that idle.  What that buys is the
 //    non-temporal load (ONCE), which reads scattered 4 KB blocks at 6.5 TB/s instead of 5.75 (and at 5.1 when an instruction
-//    takes half lines): 537 MB 103.8 -> 87.9 us, 268 MB 56.7 -> 49.3, 134 MB 29.4 -> 25.8.  The four groups of 8 tokens are chosen so that lane (g, q) ends up with the scores of the 8 consecutive tokens
-//    8q..8q+7 of its head: exactly the B-fragment the O^T MFMA needs.  Probabilities never leave registers.
+//    takes half lines): 537 MB 103.8 -> 87.9 us, 268 MB 56.7 -> 49.3, 134 MB 29.4 -> 25.8.  So it is after a window that has prefetched
+//    part of them: eight layers of the 70B-shaped TP=8 shard, cache-only, ordinary / non-temporal, batch 8 861 / 855 us, batch 32 1322 / 1313;
+//    12 of the 8B-shaped one, batch 16 of 8k tokens 1629 / 1613, batch 64 of 2k 1790 / 1777.  The four groups of 8 tokens are chosen so
+//    that lane (g, q) ends up with the scores of the 8 consecutive tokens 8q..8q+7 of its head: exactly the B-fragment the O^T MFMA
+//    needs.  Probabilities never leave registers.
 //  * epilogue: the 4 waves merge through LDS and the workgroup stores one partial (max, sum, O);
 //    k_attn_merge then combines the partials of a (sequence, kv head) in chunk order.
 //
@@ -1056,9 +1059,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_q8(AttnArgs a)
     }
 }
 
-// Merge of the chunk partials of one (sequence, query head): grid (heads of a group, kv heads,
-// batch), W waves of 64 lanes x 2 channels.  Wave w
-// takes chunks w, w + W, ...: its first two, and the (max, sum) pairs of the first sixteen, do not wait for the number of chunks, so
+// Merge of the chunk partials of one (sequence, query head): grid (heads of a group, kv heads, batch), W waves of 64 lanes x 2
+// channels.  Wave w takes chunks w, w + W, ...: its first two, and the (max, sum) pairs of the first sixteen, do not wait for the number of chunks, so
 // that a sequence of up to 2 W of them costs one round trip.  Every wave forms the softmax weights for itself (no barrier before
 // the one that adds the waves' sums, in wave order).  All orders are fixed, so the result is reproducible.  Bound by launch and
 // that round trip.  Against 1024 threads a head, one channel a lane, weights by the first wave (two rounds of workgroups at batch
