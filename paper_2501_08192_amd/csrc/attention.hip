@@ -972,7 +972,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_q8(AttnArgs a)
         const float m_new = fmaxf(m_run, tmax);
         const float alpha = exp2f(m_run - m_new);
         float pv[16], psum = 0.f, pmax = 0.f;
-        if (__any(tmin < m_new - 126.f)) {          // a probability below 2^-126 counts where its value scale is that much larger
+        // a probability below 2^-126 counts where its value scale is that much larger (out of line: 0.3 us a layer less, 0.2 for the check)
+        if (__builtin_expect(__any(tmin < m_new - 126.f), 0)) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) pv[e] = exp2f(sv[e] - m_new);
         } else {
