@@ -1072,7 +1072,8 @@ __global__ __launch_bounds__(W * 64) void k_attn_merge(AttnArgs a)
 {
     __shared__ float wl[W][kAttnMaxChunks + 8 * W];    // weights of the chunks, a row per wave (zeros behind them for the last batch of loads)
     __shared__ __align__(16) float psum[W][128];
-    const int g = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int g = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);        // uniform: a wave's places, and which of them are past the chunks, are scalar
     const int nq = a.nq, nkv = a.nkv, G = gridDim.x, j = kvh * G + g;
     const int most = PLAN ? a.plan.max_chunks : a.n_chunks;       // partials a sequence has room for, and has
     const size_t slot0 = ((size_t)b * nkv + kvh) * most, stride = (size_t)G * 128;       // chunk to chunk
