@@ -76,7 +76,7 @@ import json
 import os
 
 GOLDEN = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "measured_mi355x.json")
-TOL = 0.12      # relative error allowed per row and mode (worst: 8.4 %, batch 64 at 4k tokens; c1: 5.8 %)
+TOL = 0.12      # relative error allowed per row and mode (worst: 8.2 %, batch 64 at 4k tokens; c1: 7.5 %)
 
 
 def _golden():
@@ -148,7 +148,7 @@ def test_calibrated_model_finds_the_budget_knee_of_the_kv_dominated_workload():
             if meas[mb] < 0.95:
                 assert pred[mb] < 1.0, (win, mb)
             # up to the 256 MB of the memory-side cache the model is within 0.02; budgets beyond it thrash the cache, which the
-            # model does not know: it says 0.88 where 600 MB in a 20 us window measure 0.82 (worst: 0.064)
+            # model does not know: it says 0.85 where 600 MB in a 20 us window measure 0.83 (worst: 0.023)
             tol = 0.03 if mb <= 256 else 0.08
             assert abs(pred[mb] - meas[mb]) < tol, (win, mb, pred[mb], meas[mb])
         # prefetch time of the model's pick ~ the window (within a factor of two: the budgets are a coarse grid)
