@@ -1,5 +1,5 @@
 """A page-table entry outside the pool is a block of zeros: never followed, wherever in a wave's tiles it lies.  The same bits as with
-the entry pointing to a block that holds zeros, for chunks of one to six tiles a wave with ragged ends, on the vector and on the
+the entry pointing to a block that holds zeros, for chunks of one to twelve tiles a wave (int8 six) with ragged ends, on the vector and on the
 matrix-core path, for every cache format."""
 import pytest
 import torch

@@ -17,7 +17,7 @@ def _same_bits(layers, weights_once, kv_once, *shape, **formats):
     for n_layers in layers:
         w = synth.Workload("once", n_layers, *shape, (8.0, 8.0), **formats)
         with Session(w, seed=29, layers=[0]) as s:
-            s.seq_lens.copy_(torch.tensor([w.context - 11 * b for b in range(w.batch)], dtype=torch.int32))
+            s.seq_lens.copy_(torch.tensor([max(1, w.context - 11 * b) for b in range(w.batch)], dtype=torch.int32))
             out = [s.run().clone()]
             s.set_policy(default_policy(w, budget_bytes=1 << 40))
             out.append(s.run().clone())
@@ -42,6 +42,13 @@ def test_same_bits_as_the_only_layer_and_as_the_first_of_many(batch, weights, kv
 @pytest.mark.parametrize("batch,weights", [(1, "bf16"), (2, "bf16"), (1, "int8")])
 def test_same_bits_with_two_passes_of_weights_in_flight(batch, weights):
     _same_bits((1, 8), True, True, 4096, 8, 2, 128, 3584, batch, 100, False, weight_format=weights)       # 109 MB a layer in bf16
+
+
+@pytest.mark.parametrize("batch", [5, 17, 33, 64])
+@pytest.mark.parametrize("weights", ["bf16", "int8"])
+def test_same_bits_over_long_ranges(batch, weights):
+    """Ranges of up to eleven int8 blocks or twenty-two slabs: several rounds of the rings of weights in flight, and their remainders."""
+    _same_bits((1, 4), True, True, 4096, 2, 1, 128, 9472, batch, 90, False, weight_format=weights, kv_format="bf16", weight_layout="tiled")     # 240 MB a layer in bf16
 
 
 def test_same_bits_where_only_the_cache_exceeds_it():
